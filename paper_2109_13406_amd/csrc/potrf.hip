@@ -152,13 +152,17 @@ template <bool TWO>
 __global__ void __launch_bounds__(PANEL_THREADS)
 dd_potrf_panel(const double* __restrict__ s_hi, const double* __restrict__ s_lo, int64_t lds,
                double* __restrict__ a_hi, double* __restrict__ a_lo, int64_t lda, int64_t rows,
-               int jb, int upper, long long* __restrict__ info, long long offset) {
+               int jb, int upper, long long* info, long long offset) {
   __shared__ PanelSmem sm;
   // the critical path of the factorisation, beside the workgroups of the bulk
   // update: issue first
   __builtin_amdgcn_s_setprio(3);
-  // an earlier block of this factorisation failed: leave this one alone
-  if (*info != 0) return;
+  // An earlier block of this factorisation failed: leave this one alone.  A
+  // failure of this very block, which workgroup 0 may be recording already
+  // (offset + its pivot's order), does not count: every wave of every workgroup
+  // takes the same way whatever it reads, and finds that pivot itself.
+  const long long before = __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (before != 0 && before <= offset) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int t = tid; t < PANEL_MAX * PANEL_MAX; t += PANEL_THREADS) {
@@ -250,7 +254,8 @@ dd_potrf_panel(const double* __restrict__ s_hi, const double* __restrict__ s_lo,
     }
   }
   if (fail) {
-    if (blockIdx.x == 0 && tid == 0) *info = offset + fail;
+    if (blockIdx.x == 0 && tid == 0)
+      __hip_atomic_store(info, offset + fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
 
