@@ -25,7 +25,7 @@
 // Rows below.  A row p takes p(l) -= p(c) U(l,c) for l > c, column after
 // column, with U(l,c) = L(l,c) / L(c,c) in LDS, and L(i,c) = p(c) / L(c,c) at
 // the end: one or two rows per wave, lane = column, p(c) broadcast through scalar
-// registers.  Substitution needs no inverse of the block (half of the work of
+// registers.  (All of it on values scaled by powers of two: panel_scale.)  Substitution needs no inverse of the block (half of the work of
 // its elimination before) and no product launch.
 //
 // Every workgroup factors the diagonal block for itself (they would wait for
@@ -97,7 +97,22 @@ struct PanelSmem {
   double2 inv[PANEL_MAX];                    // 1 / L(c,c)
   double2 l[PANEL_MAX][PANEL_MAX + 1];       // [column][row]: the block, then X, then U
   double2 rows[PANEL_MAX][PANEL_ROWS + 1];   // [column][row]: the rows being solved
+  int sc[PANEL_MAX];                         // scale exponents (see panel_scale)
 };
+
+// The exponent s of row (and column) i of the diagonal block: the elimination
+// runs on L(i,l) 2^(s_i + s_l), whose diagonal lies in [1/4, 2).  Without it
+// the low part of a reciprocal 1 / d falls below the binary64 range from d =
+// 2^968 on (an order 150 matrix scaled by 2^994: 2.5e5 instead of 0.31 units
+// 2^-104 of the factor's norm); a square root and a division, which need no
+// scaling, are twice as long in the chain.
+__device__ __forceinline__ int panel_scale(double d) {
+  return d > 0.0 && d < __builtin_inf() ? -(__builtin_amdgcn_frexp_exp(d) >> 1) : 0;
+}
+
+__device__ __forceinline__ double2 scaled(double2 v, int e) {
+  return make_double2(ldexp(v.x, e), ldexp(v.y, e));
+}
 
 // Columns c0 .. c1-1, with the entries J .. PANEL_SLOTS-1 of every thread;
 // returns 0, or 1 + the column of the first failing pivot.
@@ -170,7 +185,9 @@ dd_potrf_panel(const double* __restrict__ s_hi, const double* __restrict__ s_lo,
     const int i = upper ? q : p, l = upper ? p : q;
     if (i >= jb || l > i) continue;
     const int64_t o = lv(upper, i, l, lds);
-    sm.l[l][i] = make_double2(s_hi[o], s_lo[o]);
+    const double2 v = make_double2(s_hi[o], s_lo[o]);
+    sm.l[l][i] = v;
+    if (i == l) sm.sc[i] = panel_scale(v.x);
   }
   __syncthreads();
 
@@ -190,10 +207,12 @@ dd_potrf_panel(const double* __restrict__ s_hi, const double* __restrict__ s_lo,
     const bool on = q >= 0;
     sl[j] = on ? jb - 1 - r : -1;
     si[j] = on ? jb - 1 - (q - r * (r + 1) / 2) : 0;
-    const double2 v = on ? sm.l[sl[j]][si[j]] : make_double2(0.0, 0.0);
+    const double2 v = on ? scaled(sm.l[sl[j]][si[j]], sm.sc[si[j]] + sm.sc[sl[j]])
+                         : make_double2(0.0, 0.0);
     z[j] = ddv{v.x, v.y};
     if (sl[j] == 0) {
       sm.x[0][si[j]] = v;
+      sm.l[0][si[j]] = v;
       if (si[j] == 0) {
         const ddv r = dd_recip(z[j]);
         sm.rd[0] = make_double2(r.hi, r.lo);
@@ -248,9 +267,13 @@ dd_potrf_panel(const double* __restrict__ s_hi, const double* __restrict__ s_lo,
       sm.l[l][i] = make_double2(u.hi, u.lo);
     }
     if (blockIdx.x == 0) {
+      // back from the scaled values: the factor, and the failing column's X
+      // (columns after it are as they were read)
+      const int e = l < done ? sm.sc[i] : l == done ? sm.sc[i] + sm.sc[l] : 0;
+      const double2 w = scaled(make_double2(v.hi, v.lo), -e);
       const int64_t o = lv(upper, i, l, lda);
-      a_hi[o] = v.hi;
-      a_lo[o] = v.lo;
+      a_hi[o] = w.x;
+      a_lo[o] = w.y;
     }
   }
   if (fail) {
@@ -269,7 +292,7 @@ dd_potrf_panel(const double* __restrict__ s_hi, const double* __restrict__ s_lo,
       double2 v = make_double2(0.0, 0.0);
       if (l < jb && r0 + i < below) {
         const int64_t o = lv(upper, jb + r0 + i, l, lds);
-        v = make_double2(s_hi[o], s_lo[o]);
+        v = scaled(make_double2(s_hi[o], s_lo[o]), sm.sc[l]);
       }
       sm.rows[l][i] = v;
     }
