@@ -474,6 +474,9 @@ int mpdd_ozaki_split(mpdd_handle h, int algo, const char *trans, mpdd_int rows, 
  * when the server is idle (nothing queued or admitted, a slot free) and the
  * submitting thread has the server's device current, submit launches the
  * request itself instead of handing it to the scheduler thread.
+ * A group whose launch fails before any of its kernels is enqueued is run
+ * again request by request; one that fails after that returns MPDD_ERR_HIP for
+ * all its requests (their C may or may not be updated, never twice).
  * The scheduler thread polls (yielding its core) while work is in flight and
  * for 50 ms after its last activity, then sleeps until the next submission.
  *

@@ -21,10 +21,13 @@ extern "C" {
  * simulated time (set by mpdd_server_set_fake_rate); h may be NULL. */
 #define MPDD_SERVER_FAKE_DEVICE 1
 
-/* mpdd_request.inject values: a forced failure of that request only. */
+/* mpdd_request.inject values: a forced failure, of that request only where not
+ * said otherwise. */
 #define MPDD_INJECT_NONE 0
 #define MPDD_INJECT_DEVICE_ERROR 1     /* its launch reports a device error (MPDD_ERR_HIP) */
 #define MPDD_INJECT_ALLOC_FAILURE 2    /* it fails admission as if out of memory */
+#define MPDD_INJECT_LATE_ERROR 3       /* its whole group's launch reports a device error
+                                          after the kernels were enqueued */
 
 /* Fake-device servers only: simulated throughput (dd-flops per second) and
  * per-group latency (seconds).  Returns 0 or MPDD_ERR_ARG. */

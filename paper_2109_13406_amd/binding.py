@@ -80,6 +80,7 @@ MPDD_SERVER_FAKE_DEVICE = 1
 MPDD_INJECT_NONE = 0
 MPDD_INJECT_DEVICE_ERROR = 1
 MPDD_INJECT_ALLOC_FAILURE = 2
+MPDD_INJECT_LATE_ERROR = 3
 
 _I = ctypes.c_int64
 _P = ctypes.c_void_p

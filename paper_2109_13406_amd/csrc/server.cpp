@@ -303,7 +303,8 @@ bool build_group(Slot& sl, const std::vector<Req*>& g, size_t& used, int counts[
 // Launch the grouped kernel of every tile shape that has items, on the slot's
 // stream behind the copy of its descriptors.  (As a captured graph of one
 // kernel per shape, empty ones included, a group cost 10 to 20 us more.)
-int launch_lists(Slot& sl, const int counts[kNumServeTiles]) {
+// *enqueued: whether any of them was launched, also where a later one fails.
+int launch_lists(Slot& sl, const int counts[kNumServeTiles], bool* enqueued) {
   const char* dbase = (const char*)sl.dev_buf;
   const GroupHeader* hdr = (const GroupHeader*)dbase;
   const ServeReq* reqs = (const ServeReq*)(dbase + sizeof(GroupHeader));
@@ -315,6 +316,7 @@ int launch_lists(Slot& sl, const int counts[kNumServeTiles]) {
     if (launch_grouped_list(kServeTiles[c], dbase, reqs, hdr->count, &hdr->items_offset, c,
                             std::min(counts[c], most), sl.stream) != hipSuccess)
       return MPDD_ERR_HIP;
+    *enqueued = true;
   }
   return 0;
 }
@@ -348,8 +350,9 @@ void free_slot(Slot& sl) {
   sl = Slot();
 }
 
-// Launch a group on a slot (called with the lock held).  Returns 0 or an error.
-int launch_group(mpdd_server_s* s, Slot& sl, std::vector<Req*>& g) {
+// Launch a group on a slot.  Returns 0 or an error; *enqueued: whether any of
+// its kernels was launched, also where a later step fails.
+int enqueue_group(mpdd_server_s* s, Slot& sl, std::vector<Req*>& g, bool* enqueued) {
   const double t0 = now_s();
   for (Req* q : g) {
     q->t.start = t0;
@@ -359,11 +362,14 @@ int launch_group(mpdd_server_s* s, Slot& sl, std::vector<Req*>& g) {
   s->stats.groups += 1;
   for (Req* q : g)
     if (q->r.inject == MPDD_INJECT_DEVICE_ERROR) return MPDD_ERR_HIP;
+  bool late = false;
+  for (Req* q : g) late = late || q->r.inject == MPDD_INJECT_LATE_ERROR;
   if (s->fake) {
     double flops = 0.0;
     for (Req* q : g) flops += q->flops;
     sl.fake_done = t0 + s->fake_latency + flops / s->fake_rate;
-    return 0;
+    *enqueued = true;
+    return late ? MPDD_ERR_HIP : 0;
   }
   if (g.size() == 1) {
     // a group of one: launch its tile kernel directly with the update passed
@@ -378,7 +384,8 @@ int launch_group(mpdd_server_s* s, Slot& sl, std::vector<Req*>& g) {
     p.tiles_m = (int)((m + ti->bm - 1) / ti->bm);
     p.tiles_n = (int)((n + ti->bn - 1) / ti->bn);
     if (launch_gemm(tile, p, ta, tb, false, 1, sl.stream) != hipSuccess) return MPDD_ERR_HIP;
-    if (hipEventRecord(sl.done_ev, sl.stream) != hipSuccess) return MPDD_ERR_HIP;
+    *enqueued = true;
+    if (late || hipEventRecord(sl.done_ev, sl.stream) != hipSuccess) return MPDD_ERR_HIP;
     return 0;
   }
   size_t used = 0;
@@ -387,9 +394,20 @@ int launch_group(mpdd_server_s* s, Slot& sl, std::vector<Req*>& g) {
   if (hipMemcpyAsync(sl.dev_buf, sl.host_buf, used, hipMemcpyHostToDevice, sl.stream) !=
       hipSuccess)
     return MPDD_ERR_HIP;
-  if (const int e = launch_lists(sl, counts)) return e;
-  if (hipEventRecord(sl.done_ev, sl.stream) != hipSuccess) return MPDD_ERR_HIP;
+  if (const int e = launch_lists(sl, counts, enqueued)) return e;
+  if (late || hipEventRecord(sl.done_ev, sl.stream) != hipSuccess) return MPDD_ERR_HIP;
   return 0;
+}
+
+// enqueue_group (called with the lock held).  A group that fails after some of
+// its kernels were launched (*enqueued) has updated some of its C already: it
+// is over when this returns (the stream is waited for, since the callers may
+// then free the operands), and must not run again.
+int launch_group(mpdd_server_s* s, Slot& sl, std::vector<Req*>& g, bool* enqueued) {
+  *enqueued = false;
+  const int rc = enqueue_group(s, sl, g, enqueued);
+  if (rc != 0 && *enqueued && !s->fake) (void)hipStreamSynchronize(sl.stream);
+  return rc;
 }
 
 void release(mpdd_server_s* s, Req* q) {
@@ -465,8 +483,9 @@ void scheduler(mpdd_server_s* s) {
         continue;
       }
       s->admitted.erase(s->admitted.begin(), s->admitted.begin() + take);
-      int rc = launch_group(s, *free_sl, g);
-      if (rc != 0 && g.size() > 1) {
+      bool enqueued;
+      int rc = launch_group(s, *free_sl, g, &enqueued);
+      if (rc != 0 && g.size() > 1 && !enqueued) {
         // isolate the failure: run the requests one by one.  The slot stays
         // marked busy meanwhile (holding no requests), so the submit path,
         // which may run while the fake device's wait below drops the lock,
@@ -474,7 +493,7 @@ void scheduler(mpdd_server_s* s) {
         free_sl->busy = true;
         for (Req* q : g) {
           std::vector<Req*> one{q};
-          int r1 = launch_group(s, *free_sl, one);
+          int r1 = launch_group(s, *free_sl, one, &enqueued);
           if (r1 == 0 && !s->fake) {
             hipError_t w = hipEventSynchronize(free_sl->done_ev);
             if (w != hipSuccess) r1 = MPDD_ERR_HIP;
@@ -491,8 +510,12 @@ void scheduler(mpdd_server_s* s) {
         free_sl->busy = false;
         s->cv_done.notify_all();
       } else if (rc != 0) {
-        finish(s, g[0], rc, now_s());
-        release(s, g[0]);
+        // (which of a partly launched group's requests were updated is unknown)
+        const double t_end = now_s();
+        for (Req* q : g) {
+          finish(s, q, rc, t_end);
+          release(s, q);
+        }
         s->cv_done.notify_all();
       } else {
         free_sl->reqs = g;
@@ -547,7 +570,8 @@ bool launch_from_submit(mpdd_server_s* s, Req* q) {
   s->inflight_bytes += q->bytes;
   s->inflight_count += 1;
   std::vector<Req*> g{q};
-  const int rc = launch_group(s, *free_sl, g);
+  bool enqueued;
+  const int rc = launch_group(s, *free_sl, g, &enqueued);
   if (rc != 0) {
     finish(s, q, rc, now_s());
     release(s, q);
