@@ -47,7 +47,7 @@ class ScratchCache {
       // (the event, not the handle's value, is the order: a destroyed
       // stream's handle may come back)
       const hipError_t e = hipStreamWaitEvent(st, own->done, 0);
-      if (e != hipSuccess) return e;
+      if (e != hipSuccess) return cleared(e);
       return take(*own, p, st);
     }
     if (other) return take(*other, p, st);
@@ -70,13 +70,13 @@ class ScratchCache {
     }
     if (e != hipSuccess) {
       (void)hipFreeAsync(b.ptr, st);
-      return e;
+      return cleared(e);
     }
     blocks_.push_back(b);
     return take(blocks_.back(), p, st);
   }
 
-  // The work on st so far is the last to use p.
+  // The work on st so far is the last to use p.  (No error left pending.)
   hipError_t put(void* p, hipStream_t st) {
     if (!p) return hipSuccess;
     std::lock_guard<std::mutex> lk(mu_);
@@ -87,7 +87,7 @@ class ScratchCache {
       else if (!blocks_[i].busy)
         ++free_blocks;
     }
-    if (at == blocks_.size()) return hipFreeAsync(p, st);   // taken under capture
+    if (at == blocks_.size()) return cleared(hipFreeAsync(p, st));   // taken under capture
     Block& b = blocks_[at];
     const hipError_t e = hipEventRecord(b.done, st);
     b.busy = false;
@@ -95,7 +95,7 @@ class ScratchCache {
       (void)hipEventDestroy(b.done);
       const hipError_t f = hipFreeAsync(p, st);
       blocks_.erase(blocks_.begin() + at);
-      return e != hipSuccess ? e : f;
+      return cleared(e != hipSuccess ? e : f);
     }
     return hipSuccess;
   }
@@ -150,10 +150,15 @@ class ScratchCache {
     return (bytes + step - 1) / step * step;
   }
 
-  hipError_t pool_alloc(void** p, size_t bytes, hipStream_t st) {
-    const hipError_t e = hipMallocFromPoolAsync(p, bytes, pool_, st);
+  // An error that this class reports itself: a later launch's check must not
+  // find it again.
+  static hipError_t cleared(hipError_t e) {
     if (e != hipSuccess) (void)hipGetLastError();
     return e;
+  }
+
+  hipError_t pool_alloc(void** p, size_t bytes, hipStream_t st) {
+    return cleared(hipMallocFromPoolAsync(p, bytes, pool_, st));
   }
 
   hipError_t take(Block& b, void** p, hipStream_t st) {
@@ -166,7 +171,8 @@ class ScratchCache {
   // Block i (free) back to the pool, after its last use.
   void drop(size_t i, hipStream_t st) {
     Block& b = blocks_[i];
-    if (hipStreamWaitEvent(st, b.done, 0) != hipSuccess) (void)hipEventSynchronize(b.done);
+    if (cleared(hipStreamWaitEvent(st, b.done, 0)) != hipSuccess)
+      (void)hipEventSynchronize(b.done);
     (void)hipFreeAsync(b.ptr, st);
     (void)hipEventDestroy(b.done);
     blocks_.erase(blocks_.begin() + i);
