@@ -51,7 +51,9 @@
  * stream-ordered memory pool on that device: scratch memory that a call
  * needs (split-k partial sums, split-form slices, ...) comes from blocks that
  * the handle keeps between calls, or is allocated from the pool on the call's
- * stream; both keep released memory for later calls until mpdd_destroy.  Calls
+ * stream.  The handle keeps up to 8 free blocks and 8 GiB of them (or one larger
+ * block) for later calls, the pool up to 8 GiB more; the rest goes back to the
+ * driver at a later synchronisation, everything with mpdd_destroy.  Calls
  * on one handle may be made from several host threads and streams at once.
  */
 #ifndef MPDD_H

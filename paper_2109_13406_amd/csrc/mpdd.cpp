@@ -96,9 +96,9 @@ struct mpdd_handle_s {
   TuneTable tune;
   // Stream-ordered scratch (k-split partials, split-form slices, Cgemm
   // planes, Rpotrf panels): blocks kept between calls (scratch.hpp), from the
-  // handle's own pool, which keeps freed memory instead of returning it to the
-  // driver at every synchronisation, and also serves the host staging.  Both
-  // hold their peak size until mpdd_destroy.
+  // handle's own pool, which keeps up to as much freed memory again instead of
+  // returning it to the driver at every synchronisation, and also serves the
+  // host staging.
   ScratchCache scratch;
   hipMemPool_t pool = nullptr;
   std::mutex host_mu;           // serialises the host-pointer calls on this handle
@@ -497,7 +497,7 @@ int mpdd_create(mpdd_handle* h, const char* tuner_cache_path) {
   props.allocType = hipMemAllocationTypePinned;
   props.location.type = hipMemLocationTypeDevice;
   props.location.id = s->device;
-  uint64_t keep = UINT64_MAX;
+  uint64_t keep = ScratchCache::KEEP_BYTES;
   if (hipMemPoolCreate(&s->pool, &props) != hipSuccess ||
       hipMemPoolSetAttribute(s->pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
     if (s->pool) (void)hipMemPoolDestroy(s->pool);

@@ -9,13 +9,16 @@
 // its next use after its last one, whatever the streams: a block last used on
 // the caller's own stream is taken first (the wait is then in order), one of
 // another stream only once its work is done, so that calls on different
-// streams do not wait for each other.  Blocks are given back to the pool when
-// more than KEEP are free, when one of the caller's stream is too small, when
-// an allocation fails, and with the handle.  A stream under capture uses the
-// pool itself (its allocations become graph nodes).
+// streams do not wait for each other.  Free blocks are given back to the pool,
+// those unused for longest first, when there are more than KEEP of them or they
+// hold more than KEEP_BYTES (one block may hold more by itself: a call that
+// needs it would need it again); when one of the caller's stream is too small;
+// when an allocation fails; and with the handle.  A stream under capture uses
+// the pool itself (its allocations become graph nodes).
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <mutex>
 #include <vector>
@@ -24,6 +27,8 @@ namespace mpdd {
 
 class ScratchCache {
  public:
+  static constexpr size_t KEEP_BYTES = (size_t)8 << 30;
+
   void open(hipMemPool_t pool) { pool_ = pool; }
 
   // `bytes` bytes for work enqueued on st until put(): *p, or an error with no
@@ -80,24 +85,36 @@ class ScratchCache {
   hipError_t put(void* p, hipStream_t st) {
     if (!p) return hipSuccess;
     std::lock_guard<std::mutex> lk(mu_);
-    size_t free_blocks = 0, at = blocks_.size();
+    size_t at = blocks_.size(), count = 0, bytes = 0;
     for (size_t i = 0; i < blocks_.size(); ++i) {
-      if (blocks_[i].ptr == p)
-        at = i;
-      else if (!blocks_[i].busy)
-        ++free_blocks;
+      if (blocks_[i].ptr == p) at = i;
+      if (blocks_[i].ptr == p || !blocks_[i].busy) {
+        ++count;
+        bytes += blocks_[i].bytes;
+      }
     }
     if (at == blocks_.size()) return cleared(hipFreeAsync(p, st));   // taken under capture
-    Block& b = blocks_[at];
-    const hipError_t e = hipEventRecord(b.done, st);
+    // (in the order of their last use)
+    std::rotate(blocks_.begin() + at, blocks_.begin() + at + 1, blocks_.end());
+    Block& b = blocks_.back();
+    hipError_t e = hipEventRecord(b.done, st);
     b.busy = false;
-    if (e != hipSuccess || free_blocks >= KEEP) {
-      (void)hipEventDestroy(b.done);
-      const hipError_t f = hipFreeAsync(p, st);
-      blocks_.erase(blocks_.begin() + at);
-      return cleared(e != hipSuccess ? e : f);
+    auto over = [&] { return count > KEEP || (count > 1 && bytes > KEEP_BYTES); };
+    if (e == hipSuccess) {
+      // the oldest ones whose work is done (the others' streams are not waited for)
+      for (size_t i = 0; over() && i + 1 < blocks_.size();) {
+        if (blocks_[i].busy || !idle(blocks_[i])) {
+          ++i;
+          continue;
+        }
+        --count;
+        bytes -= blocks_[i].bytes;
+        (void)release(i, st);
+      }
+      if (!over()) return hipSuccess;
     }
-    return hipSuccess;
+    const hipError_t f = release(blocks_.size() - 1, st);
+    return cleared(e != hipSuccess ? e : f);
   }
 
   // Every block back to the pool (no call in flight).
@@ -173,9 +190,15 @@ class ScratchCache {
     Block& b = blocks_[i];
     if (cleared(hipStreamWaitEvent(st, b.done, 0)) != hipSuccess)
       (void)hipEventSynchronize(b.done);
-    (void)hipFreeAsync(b.ptr, st);
-    (void)hipEventDestroy(b.done);
+    (void)release(i, st);
+  }
+
+  // Block i back to the pool: its work is done, or enqueued on st.
+  hipError_t release(size_t i, hipStream_t st) {
+    const hipError_t e = hipFreeAsync(blocks_[i].ptr, st);
+    (void)hipEventDestroy(blocks_[i].done);
     blocks_.erase(blocks_.begin() + i);
+    return e;
   }
 
   std::mutex mu_;

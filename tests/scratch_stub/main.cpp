@@ -48,9 +48,80 @@ static int errors() {
   return 0;
 }
 
+// Free blocks: at most 8, and 8 GiB where they are more than one.
+static int bounds() {
+  const size_t GB = (size_t)1 << 30;
+  {
+    // streams at work at once, 3 GiB each: nobody's work is waited for
+    ScratchCache c;
+    StubStream s[6];
+    std::vector<void*> p(6);
+    for (int i = 0; i < 6; ++i) {
+      CHECK(c.get(&p[i], 3 * GB, &s[i]) == hipSuccess);
+      s[i].pending = true;
+    }
+    const int waits = stub::calls["wait"] + stub::calls["sync"] + stub::calls["event_sync"];
+    for (int i = 0; i < 6; ++i) CHECK(c.put(p[i], &s[i]) == hipSuccess);
+    CHECK(waits == stub::calls["wait"] + stub::calls["sync"] + stub::calls["event_sync"]);
+    CHECK(stub::total() <= 8 * GB);
+    c.close();
+    CHECK(stub::live.empty());
+  }
+  {
+    // one after the other on streams of their own: the newest stay
+    ScratchCache c;
+    StubStream s[20];
+    void* p = nullptr;
+    size_t last = 0;
+    for (int i = 0; i < 20; ++i) {
+      const size_t n = ((size_t)(20 + i)) << 26;     // 1.25 to 2.4 GiB, each too small for the next
+      CHECK(c.get(&p, n, &s[i]) == hipSuccess);
+      CHECK(c.put(p, &s[i]) == hipSuccess);
+      last = n;
+      CHECK(stub::total() <= 8 * GB && stub::live.size() <= 8);
+    }
+    const int mallocs = stub::calls["malloc"];
+    CHECK(c.get(&p, last, &s[19]) == hipSuccess && stub::calls["malloc"] == mallocs);
+    CHECK(c.put(p, &s[19]) == hipSuccess);
+    // a single block beyond the bound is kept, and takes the others' place
+    for (int rep = 0; rep < 3; ++rep) {
+      CHECK(c.get(&p, 20 * GB, &s[0]) == hipSuccess);
+      CHECK(c.put(p, &s[0]) == hipSuccess);
+      CHECK(stub::live.size() == 1 && stub::total() >= 20 * GB);
+    }
+    CHECK(stub::calls["malloc"] == mallocs + 1);
+    CHECK(c.get(&p, 1 << 20, &s[1]) == hipSuccess);  // (its block is used, not another)
+    CHECK(c.put(p, &s[1]) == hipSuccess);
+    CHECK(stub::live.size() == 1);
+    c.close();
+    CHECK(stub::live.empty());
+  }
+  {
+    // many small ones, more in use than are kept
+    ScratchCache c;
+    StubStream s;
+    std::vector<void*> p(30);
+    for (auto& x : p) CHECK(c.get(&x, 1 << 20, &s) == hipSuccess);
+    CHECK(stub::live.size() == 30);
+    for (auto& x : p) CHECK(c.put(x, &s) == hipSuccess);
+    CHECK(stub::live.size() == 8);
+    // under capture: the pool itself
+    s.capturing = true;
+    void* q = nullptr;
+    CHECK(c.get(&q, 1 << 20, &s) == hipSuccess);
+    CHECK(stub::live.size() == 9);
+    CHECK(c.put(q, &s) == hipSuccess);
+    CHECK(stub::live.size() == 8);
+    c.close();
+    CHECK(stub::live.empty());
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!std::strcmp(argv[i], "errors") && errors()) return 1;
+    if (!std::strcmp(argv[i], "bounds") && bounds()) return 1;
   }
   std::printf("ok\n");
   return 0;
