@@ -370,7 +370,8 @@ int mpdd_Qgemm_ex(mpdd_handle h, const mpdd_opts *opts, const char *transa, cons
  * blocks and at the end, so it is synchronous: it returns when A is factored
  * (or a failing pivot has been found).  Device scratch of 48*nb*n + 256
  * bytes, plus the k-split partial sums of the update products (stream
- * ordered). */
+ * ordered).  Returns MPDD_ERR_HIP, with nothing enqueued, on a stream that is
+ * being captured into a graph. */
 int mpdd_Rpotrf(mpdd_handle h, const char *uplo, mpdd_int n, double *A_hi, double *A_lo,
                 mpdd_int lda, mpdd_int *info, void *stream);
 

@@ -1009,6 +1009,9 @@ int mpdd_Rpotrf_ex(mpdd_handle h, const mpdd_opts* opts, const char* uplo, mpdd_
   if (n == 0) return 0;
   if (!A_hi || !A_lo) return MPDD_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
+  // (the host reads the failure word, which a capture refuses: say so before the
+  // handle's streams and events become part of it)
+  if (ScratchCache::capturing(st)) return MPDD_ERR_HIP;
   PotrfRun run;
   int rc = run.open(h, upper, n, lda, nb, st);
   if (!rc && algo == MPDD_PLAIN) {
