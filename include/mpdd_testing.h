@@ -1,8 +1,9 @@
 /*
- * mpdd_testing.h -- test hooks of libmpdd's request server (mpdd.h).
+ * mpdd_testing.h -- test hooks of libmpdd (mpdd.h).
  *
  * For tests of the server's scheduling and failure paths that must run
- * without a GPU or must force a failure from the host.  Not part of the
+ * without a GPU or must force a failure from the host, and for tests that must
+ * know which way a call takes.  Not part of the
  * product interface: production callers pass flags = 0 to
  * mpdd_server_create and leave mpdd_request.inject at 0.  The hooks live in
  * the same library (one build), and are declared here so that mpdd.h shows
@@ -32,6 +33,15 @@ extern "C" {
 /* Fake-device servers only: simulated throughput (dd-flops per second) and
  * per-group latency (seconds).  Returns 0 or MPDD_ERR_ARG. */
 int mpdd_server_set_fake_rate(mpdd_server s, double dd_flops_per_s, double group_latency_s);
+
+/* The way that a call without options takes, by size alone (not under capture,
+ * scratch to be had): 0 the plain kernels, 1 the guarded modular form, 2 its form
+ * for one long operand.  op: MPDD_OP_GEMM or MPDD_OP_SYRK, or MPDD_TEST_CGEMM or
+ * MPDD_TEST_QGEMM (m, n, k of the product, Rsyrk m = n).  tile, splitk (may be
+ * NULL): the plain kernels' tile-table entry and k-split of that size. */
+#define MPDD_TEST_CGEMM 16
+#define MPDD_TEST_QGEMM 17
+int mpdd_test_route(int op, mpdd_int m, mpdd_int n, mpdd_int k, int *tile, int *splitk);
 
 #ifdef __cplusplus
 }

@@ -81,6 +81,8 @@ MPDD_INJECT_NONE = 0
 MPDD_INJECT_DEVICE_ERROR = 1
 MPDD_INJECT_ALLOC_FAILURE = 2
 MPDD_INJECT_LATE_ERROR = 3
+MPDD_TEST_CGEMM = 16
+MPDD_TEST_QGEMM = 17
 
 _I = ctypes.c_int64
 _P = ctypes.c_void_p
@@ -141,6 +143,8 @@ SIGNATURES = {
     "mpdd_server_poll": (ctypes.c_int, [_P, ctypes.c_uint64, ctypes.POINTER(ctypes.c_int)]),
     "mpdd_server_get_stats": (ctypes.c_int, [_P, ctypes.POINTER(mpdd_server_stats)]),
     "mpdd_server_destroy": (ctypes.c_int, [_P]),
+    "mpdd_test_route": (ctypes.c_int, [ctypes.c_int, _I, _I, _I, ctypes.POINTER(ctypes.c_int),
+                                       ctypes.POINTER(ctypes.c_int)]),
     "mpdd_tile_count": (ctypes.c_int, []),
     "mpdd_tile_info": (ctypes.c_int, [ctypes.c_int] + [ctypes.POINTER(ctypes.c_int)] * 4),
 }
@@ -602,6 +606,14 @@ def mpdd_server_create(h, hbm_budget_bytes, max_inflight, flags=0):
     if info != 0:
         raise RuntimeError(f"mpdd_server_create failed: {info}")
     return s
+
+
+def mpdd_test_route(op, m, n, k):
+    """(route, tile, splitk): 0 plain, 1 guarded modular, 2 its long form, of a
+    call without options; the tile and k-split of the plain kernels."""
+    tile, split = ctypes.c_int(), ctypes.c_int()
+    route = load().mpdd_test_route(op, m, n, k, ctypes.byref(tile), ctypes.byref(split))
+    return route, tile.value, split.value
 
 
 def mpdd_server_set_fake_rate(s, dd_flops_per_s, group_latency_s):

@@ -24,9 +24,11 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "dd.hpp"
 #include "kernels.hpp"
+#include "tuner.hpp"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -52,9 +54,8 @@ __device__ __forceinline__ int tri_col(int t) {
   return y;
 }
 
-__device__ __forceinline__ bool tile_coords(const GemmParams& p, int& bi, int& bj) {
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
+// Tile of the b-th of nb (tile_blocks) workgroups; false: outside the triangle.
+__device__ __forceinline__ bool tile_coords(const GemmParams& p, int b, int nb, int& bi, int& bj) {
   if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
   const bool blocks8 = (p.tiles_m & 7) == 0 && (p.tiles_n & 7) == 0;
   if (p.tri == 0) {
@@ -360,6 +361,15 @@ __device__ __forceinline__ ddv c_input(const GemmParams& p, int64_t i, int64_t j
   return {p.c_hi[i + j * p.ldc], p.c_lo[i + j * p.ldc]};
 }
 
+// C(i, j) <- alpha*acc + beta*C(i, j)
+__device__ __forceinline__ void store_entry(const GemmParams& p, int64_t i, int64_t j, ddv acc) {
+  ddv v = dd_mul(ddv{p.alpha_hi, p.alpha_lo}, acc);
+  const int64_t ci = i + j * p.ldc;
+  if (!p.beta_zero) v = dd_add(v, dd_mul(ddv{p.beta_hi, p.beta_lo}, c_input(p, i, j)));
+  p.c_hi[ci] = v.hi;
+  p.c_lo[ci] = v.lo;
+}
+
 template <int BM, int BN, int RM, int RN, bool PARTIAL, typename Wanted = AnyEntry>
 __device__ __forceinline__ void dd_tile_epilogue(const GemmParams& p, int64_t i0, int64_t j0,
                                                  int z, const double (&ch)[RM][RN],
@@ -386,14 +396,31 @@ __device__ __forceinline__ void dd_tile_epilogue(const GemmParams& p, int64_t i0
       if (p.tri == 1 && i > j) continue;
       if (p.tri == 2 && i < j) continue;
       if (!wanted(i, j)) continue;
-      ddv acc{ch[r][c], cl[r][c]};
-      ddv v = dd_mul(ddv{p.alpha_hi, p.alpha_lo}, acc);
-      const int64_t ci = i + j * p.ldc;
-      if (!p.beta_zero) v = dd_add(v, dd_mul(ddv{p.beta_hi, p.beta_lo}, c_input(p, i, j)));
-      p.c_hi[ci] = v.hi;
-      p.c_lo[ci] = v.lo;
+      store_entry(p, i, j, ddv{ch[r][c], cl[r][c]});
     }
   }
+}
+
+// Sum of the S partials of an entry (S a power of two), partial(s) the s-th, in
+// a balanced pairwise tree -- ((p0 + p1) + (p2 + p3)) + ... -- by a carry-save
+// stack of at most seven pending sums: the sum of the partials seen so far is held
+// as sums over runs of 2^j partials, and a new run is merged with the pending one
+// of its size before it is pushed (the earlier run always the left operand).  The
+// order does not depend on the schedule, so the result is deterministic.  S is
+// a template parameter, so the loop unrolls and the stack stays in registers.
+template <int S, typename Partial>
+__device__ __forceinline__ ddv split_sum(const Partial& partial) {
+  ddv st[7];
+  int depth = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    ddv v = partial(s);
+    // partial s closes a run of 2^t partials for every trailing one bit t of s + 1
+#pragma unroll
+    for (int t = s + 1; (t & 1) == 0; t >>= 1) v = dd_add(st[--depth], v);
+    st[depth++] = v;
+  }
+  return st[0];
 }
 
 // Small tiles, for products that give the chip few of them: the workgroup's
@@ -406,6 +433,11 @@ __device__ __forceinline__ void dd_tile_epilogue(const GemmParams& p, int64_t i0
 // by two entries a thread make 80 % of the LDS bandwidth; 4 x 2 and 4 x 4 (20
 // and 40 % fewer reads per term) measured slower everywhere, with two or three
 // waves fewer per SIMD, as did 8 and 16 groups.
+//
+// Tile-table entry 5: 16 x 16, four groups, 32-deep k-tiles.  Its accurate form,
+// whose sums run in the order of the terms, is a kernel of one entry per thread.
+constexpr int KS_TILE = 5, KS_B = 16, KS_BKG = 8, KS_R = 2, KS_KW = 4;
+
 template <int BM, int BN, int BK>
 union KSplitSmem {
   struct {
@@ -571,7 +603,7 @@ __global__ void __launch_bounds__((BM / RM) * (BN / RN) * KW, 4)
 dd_ksplit_kernel(GemmParams p) {
   __shared__ KSplitSmem<BM, BN, BKG * KW> sm;
   int bi, bj;
-  if (!tile_coords(p, bi, bj)) return;
+  if (!tile_coords(p, (int)blockIdx.x, (int)gridDim.x, bi, bj)) return;
   const int64_t i0 = (int64_t)bi * BM, j0 = (int64_t)bj * BN;
   const int64_t kbeg = (int64_t)blockIdx.z * p.kchunk;
   const int64_t kend = (kbeg + p.kchunk < p.k) ? kbeg + p.kchunk : p.k;
@@ -587,7 +619,8 @@ __global__ void __launch_bounds__((BM / RM) * (BN / RN))
 dd_gemm_kernel(GemmParams p) {
   __shared__ DDTileSmem<BM, BN, BK> sm;
   int bi, bj;
-  if (!tile_coords(p, bi, bj)) return;     // a tile outside the triangle
+  // (a tile outside the triangle)
+  if (!tile_coords(p, (int)blockIdx.x, (int)gridDim.x, bi, bj)) return;
   const int64_t i0 = (int64_t)bi * BM;
   const int64_t j0 = (int64_t)bj * BN;
   const int64_t kbeg = (int64_t)blockIdx.z * p.kchunk;
@@ -632,124 +665,6 @@ dd_grouped_kernel(const char* __restrict__ base, const ServeReq* __restrict__ re
   }
 }
 
-// The entries of C that a guarded modular product (ozaki.hip) left to the
-// plain one, in units of one BM x BM tile (64, or 32 where 64 would give the
-// chip too few).  A fixed grid looks through the bytes of the tiles' 64 x 64
-// blocks, each workgroup at the tiles blockIdx.x, + gridDim.x, ... 256 at a
-// time (one per thread).  A tile with many failed entries is computed whole,
-// as dd_gemm_kernel would, and those entries stored; with few, each wave takes
-// entries of its own: lanes take every 64th term with the accurate dd steps
-// and meet in a fixed order (at k = 512 an entry costs a wave about 3 us, a
-// 64 x 64 tile its workgroup 140 us).  Usually there are none, and the launch
-// is one load per tile: 4 us.
-template <int BM, int RM, bool XM, bool TA, bool TB>
-__global__ void __launch_bounds__(256)
-dd_gemm_failed(GemmParams p, CrtFailed failed) {
-  constexpr int SUB = 64 / BM;                   // tiles per block edge
-  __shared__ DDTileSmem<BM, BM, 16> sm;
-  __shared__ unsigned char set[256];
-  __shared__ short list[CRT_FAILED_ENTRIES];
-  __shared__ int number;
-  const int tiles = p.tiles_m * p.tiles_n, stride = (int)gridDim.x;
-  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int base = blockIdx.x; base < tiles; base += 256 * stride) {
-    const int t = base + tid * stride;
-    int n = 0;
-    if (t < tiles) {
-      const int bi = t % p.tiles_m, bj = t / p.tiles_m;
-      // (blocks outside a triangle have no byte)
-      if (!(p.tri == 1 && bi > bj) && !(p.tri == 2 && bi < bj))
-        n = failed.block[(int64_t)(bj / SUB) * failed.ldf + bi / SUB];
-    }
-    set[tid] = (unsigned char)n;
-    if (__syncthreads_count(n) == 0) continue;
-    const int nq = min(256, (tiles - base + stride - 1) / stride);
-    for (int q = 0; q < nq; ++q) {
-      if (set[q] == 0) continue;                 // (the same for every thread)
-      const int tq = base + q * stride;
-      const int64_t i0 = (int64_t)(tq % p.tiles_m) * BM, j0 = (int64_t)(tq / p.tiles_m) * BM;
-      auto wanted = [&](int64_t i, int64_t j) {
-        return i < p.m && j < p.n && !(p.tri == 1 && i > j) && !(p.tri == 2 && i < j) &&
-               failed.entry[j * failed.lde + i] != 0;
-      };
-      if (tid == 0) number = 0;
-      __syncthreads();
-      for (int e = tid; e < BM * BM; e += 256)
-        if (wanted(i0 + e % BM, j0 + e / BM)) {
-          const int at = atomicAdd(&number, 1);
-          if (at < CRT_FAILED_ENTRIES) list[at] = (short)e;
-        }
-      __syncthreads();
-      const int count = number;
-      if (count > CRT_FAILED_ENTRIES) {
-        double ch[RM][RM], cl[RM][RM];
-        dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(p, i0, j0, 0, p.k, sm, ch, cl);
-        dd_tile_epilogue<BM, BM, RM, RM, false>(p, i0, j0, 0, ch, cl, wanted);
-      } else {
-        for (int w = wave; w < count; w += 4) {
-          const int64_t i = i0 + list[w] % BM, j = j0 + list[w] / BM;
-          ddv acc{0.0, 0.0};
-          auto term = [&](int64_t l, ddv& a, ddv& b) {
-            const int64_t oa = TA ? l + i * p.lda : i + l * p.lda;
-            const int64_t ob = TB ? j + l * p.ldb : l + j * p.ldb;
-            a = ddv{p.a_hi[oa], p.a_lo[oa]};
-            b = ddv{p.b_hi[ob], p.b_lo[ob]};
-          };
-          int64_t l = lane;
-          for (; l + 192 < p.k; l += 256) {      // four terms' loads at a time
-            ddv a[4], b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) term(l + 64 * u, a[u], b[u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc = dd_add(acc, dd_mul(a[u], b[u]));
-          }
-          for (; l < p.k; l += 64) {
-            ddv a, b;
-            term(l, a, b);
-            acc = dd_add(acc, dd_mul(a, b));
-          }
-#pragma unroll
-          for (int off = 1; off < 64; off <<= 1)
-            acc = dd_add(acc, ddv{__shfl_xor(acc.hi, off), __shfl_xor(acc.lo, off)});
-          ddv v = dd_mul(ddv{p.alpha_hi, p.alpha_lo}, acc);
-          const int64_t ci = i + j * p.ldc;
-          if (!p.beta_zero)
-            v = dd_add(v, dd_mul(ddv{p.beta_hi, p.beta_lo}, ddv{p.c_hi[ci], p.c_lo[ci]}));
-          if (lane == 0) {
-            p.c_hi[ci] = v.hi;
-            p.c_lo[ci] = v.lo;
-          }
-        }
-      }
-      __syncthreads();
-    }
-    __syncthreads();
-  }
-}
-
-template <int BM, int RM, bool XM>
-static hipError_t launch_failed_t(GemmParams p, bool ta, bool tb, const CrtFailed& failed,
-                                  hipStream_t st) {
-  p.tiles_m = (int)((p.m + BM - 1) / BM);
-  p.tiles_n = (int)((p.n + BM - 1) / BM);
-  p.kchunk = p.k;
-  const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-  const int grid = (int)std::min<int64_t>(tiles, BM == 64 ? 512 : 1024);
-  auto kern = !ta ? (!tb ? dd_gemm_failed<BM, RM, XM, false, false>
-                         : dd_gemm_failed<BM, RM, XM, false, true>)
-                  : (!tb ? dd_gemm_failed<BM, RM, XM, true, false>
-                         : dd_gemm_failed<BM, RM, XM, true, true>);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, p, failed);
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm_failed(const GemmParams& p, bool ta, bool tb, const CrtFailed& failed,
-                              hipStream_t st) {
-  if (((p.m + 63) / 64) * ((p.n + 63) / 64) * (p.tri ? 1 : 2) >= 1024)
-    return launch_failed_t<64, 4, true>(p, ta, tb, failed, st);
-  return launch_failed_t<32, 2, false>(p, ta, tb, failed, st);
-}
-
 // The same for the small tile (entry 5).
 __global__ void __launch_bounds__(256, 4)
 dd_grouped_ksplit(const char* __restrict__ base, const ServeReq* __restrict__ reqs,
@@ -777,16 +692,222 @@ dd_grouped_ksplit(const char* __restrict__ base, const ServeReq* __restrict__ re
   }
 }
 
+// The entries of C that a guarded modular product (ozaki.hip) left to the
+// plain one, in units of a FailedPlan's tiles and k-ranges.  A fixed grid looks
+// through the bytes of the tiles' 64 x 64 blocks, each workgroup at the items
+// (tile, k-range) blockIdx.x, + gridDim.x, ... 256 at a time (one per thread).  A
+// tile with many failed entries is computed whole, by the steps of
+// dd_gemm_kernel, and those entries stored (SPLIT: its partial sums, and
+// dd_failed_reduce adds them); with few, each wave takes entries of its own
+// (SPLIT: a tile's workgroups share them): lanes take every 64th term with the
+// accurate dd steps and meet in a fixed order.  At k = 512 an entry costs a wave
+// about 3 us, a tile of 64 x 64 its workgroup 170 to 230 us, of 32 x 32 49 to 64,
+// of 16 x 16 15 to 22, hence FEW (and at least a row and a column of the tile: the
+// accurate steps take unnormalised pairs too).  Usually there are none, and the
+// launch is one load per tile: 4 us.
+template <int BM, int RM, bool XM, bool TA, bool TB, bool SPLIT>
+__global__ void __launch_bounds__(256, BM == 64 ? 2 : BM == 32 ? 4 : 3)
+dd_gemm_failed(GemmParams args, CrtFailed failed, int blocks, int splits, uint8_t* whole) {
+  constexpr int SUB = 64 / BM;                   // tiles per block edge
+  constexpr bool KS = BM == KS_B;
+  constexpr int FEW = KS ? 32 : BM == 32 ? 72 : 256;
+  constexpr int U = BM == 64 ? 4 : 2;
+  __shared__ std::conditional_t<KS, KSplitSmem<BM, BM, KS_BKG * KS_KW>, DDTileSmem<BM, BM, 16>> sm;
+  __shared__ unsigned char set[256];
+  __shared__ short list[FEW];
+  __shared__ int number, mine;
+  const int items = blocks * splits, stride = (int)gridDim.x;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int base = blockIdx.x; base < items; base += 256 * stride) {
+    const int t = base + tid * stride;
+    int n = 0, bi, bj;
+    // (blocks outside a triangle have no byte)
+    if (t < items && tile_coords(args, SPLIT ? t % blocks : t, blocks, bi, bj))
+      n = failed.block[(int64_t)(bj / SUB) * failed.ldf + bi / SUB];
+    set[tid] = (unsigned char)n;
+    if (__syncthreads_count(n) == 0) continue;
+    const int nq = min(256, (items - base + stride - 1) / stride);
+    for (int q = 0; q < nq; ++q) {
+      const int state = set[q];
+      if (state == 0) continue;                  // (the same for every thread)
+      // (opaque, so that the addresses made of them are not kept in registers
+      // around the loops: the tile's steps need those)
+      GemmParams p = args;
+      asm volatile("" : "+s"(p.a_hi), "+s"(p.a_lo), "+s"(p.b_hi), "+s"(p.b_lo), "+s"(p.lda),
+                        "+s"(p.ldb), "+s"(p.k));
+      const int item = base + q * stride, z = SPLIT ? item / blocks : 0;
+      (void)tile_coords(p, SPLIT ? item % blocks : item, blocks, bi, bj);
+      const int64_t i0 = (int64_t)bi * BM, j0 = (int64_t)bj * BM;
+      auto wanted = [&](int64_t i, int64_t j) {
+        return i < p.m && j < p.n && !(p.tri == 1 && i > j) && !(p.tri == 2 && i < j) &&
+               failed.entry[j * failed.lde + i] != 0;
+      };
+      if (tid == 0) number = mine = 0;
+      __syncthreads();
+      if (state != 2) {
+        for (int e = tid; e < BM * BM; e += 256)
+          if (wanted(i0 + e % BM, j0 + e / BM)) {
+            atomicAdd(&number, 1);
+            if (SPLIT && (e % BM + e / BM) % splits != z) continue;     // another range's
+            const int at = atomicAdd(&mine, 1);
+            if (at < FEW) list[at] = (short)e;
+          }
+        __syncthreads();
+      }
+      const bool all = state == 2 || number > FEW;
+      if (SPLIT && z == 0 && tid == 0) whole[bi + (int64_t)bj * p.tiles_m] = all;
+      if (all) {
+        const int64_t kbeg = (int64_t)z * p.kchunk;
+        const int64_t kend = (SPLIT && kbeg + p.kchunk < p.k) ? kbeg + p.kchunk : p.k;
+        double ch[RM][RM], cl[RM][RM];
+        if constexpr (KS)
+          dd_ksplit_mainloop<BM, BM, KS_BKG, RM, RM, KS_KW, TA, TB>(p, i0, j0, kbeg, kend, sm, ch,
+                                                                    cl);
+        else
+          dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(p, i0, j0, kbeg, kend, sm, ch,
+                                                                  cl);
+        if (!KS || tid < (BM / RM) * (BM / RM))  // (the threads that hold the sums)
+          dd_tile_epilogue<BM, BM, RM, RM, SPLIT>(p, i0, j0, z, ch, cl, wanted);
+      } else {
+        const int count = mine;
+        for (int w = wave; w < count; w += 4) {
+          const int64_t i = i0 + list[w] % BM, j = j0 + list[w] / BM;
+          ddv acc{0.0, 0.0};
+          auto term = [&](int64_t l, ddv& a, ddv& b) {
+            const int64_t oa = TA ? l + i * p.lda : i + l * p.lda;
+            const int64_t ob = TB ? j + l * p.ldb : l + j * p.ldb;
+            a = ddv{p.a_hi[oa], p.a_lo[oa]};
+            b = ddv{p.b_hi[ob], p.b_lo[ob]};
+          };
+          int64_t l = lane;
+          for (; l + 64 * (U - 1) < p.k; l += 64 * U) {     // U terms' loads at a time
+            ddv a[U], b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) term(l + 64 * u, a[u], b[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = dd_add(acc, dd_mul(a[u], b[u]));
+          }
+          for (; l < p.k; l += 64) {
+            ddv a, b;
+            term(l, a, b);
+            acc = dd_add(acc, dd_mul(a, b));
+          }
+#pragma unroll
+          for (int off = 1; off < 64; off <<= 1)
+            acc = dd_add(acc, ddv{__shfl_xor(acc.hi, off), __shfl_xor(acc.lo, off)});
+          if (lane == 0) store_entry(p, i, j, acc);
+        }
+      }
+      __syncthreads();
+    }
+    __syncthreads();
+  }
+}
+
+// The failed entries of the tiles that dd_gemm_failed computed whole, from the
+// partial sums of their k-ranges, as dd_splitk_reduce.  Four rows a thread.
+template <int S>
+__global__ void __launch_bounds__(256)
+dd_failed_reduce(GemmParams p, CrtFailed failed, int edge, const uint8_t* whole) {
+  const int64_t mq = (p.m + 3) / 4, g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= mq * p.n) return;
+  const int64_t i0 = g % mq * 4, j = g / mq;
+  // (stored for whole 64 x 64 blocks: the four rows are there)
+  const uint32_t some = *(const uint32_t*)(failed.entry + j * failed.lde + i0);
+  if (some == 0u || !whole[i0 / edge + j / edge * p.tiles_m]) return;
+  const int64_t total = p.m * p.n;
+  for (int r = 0; r < 4; ++r) {
+    const int64_t i = i0 + r;
+    if (i >= p.m || !((some >> (8 * r)) & 1u)) continue;
+    if ((p.tri == 1 && i > j) || (p.tri == 2 && i < j)) continue;
+    store_entry(p, i, j, split_sum<S>([&](int s) {
+                  const int64_t at = (int64_t)s * total + j * p.m + i;
+                  return ddv{p.w_hi[at], p.w_lo[at]};
+                }));
+  }
+}
+
+// Workgroups of a launch over the tiles of p (tri: 8 x 8 blocks over the triangle
+// where the rows are a multiple of 8).
+static int tile_blocks(int tri, int tiles_m, int tiles_n) {
+  if (tri == 0) return tiles_m * tiles_n;
+  if ((tiles_m & 7) == 0) {
+    const int s8 = tiles_m >> 3;
+    return 64 * (s8 * (s8 + 1) / 2);
+  }
+  return tiles_m * (tiles_m + 1) / 2;
+}
+
+FailedPlan failed_plan(int tri, int64_t m, int64_t n, int64_t k) {
+  TilePlan t = timed_plan(m, n, k, tri != 0, 1);
+  const TilePlan split = timed_plan(m, n, k, tri != 0, 32);
+  if (split.us < 0.8 * t.us) t = split;
+  const TileInfo* info = tile_info(t.tile);
+  FailedPlan f;
+  f.tile = t.tile;
+  f.splits = t.splitk;
+  f.kchunk = split_chunk(k, info->bk, f.splits);
+  f.tiles_m = (int)((m + info->bm - 1) / info->bm);
+  f.tiles_n = (int)((n + info->bm - 1) / info->bm);
+  f.blocks = tile_blocks(tri, f.tiles_m, f.tiles_n);
+  if (f.splits > 1) {
+    f.flag_bytes = ((size_t)f.tiles_m * f.tiles_n + 255) / 256 * 256;
+    f.bytes = f.flag_bytes + (size_t)16 * f.splits * m * n;
+  }
+  return f;
+}
+
+template <int BM, int RM, bool XM, bool SPLIT>
+static hipError_t launch_failed_t(const GemmParams& p, bool ta, bool tb, const CrtFailed& failed,
+                                  const FailedPlan& plan, uint8_t* whole, hipStream_t st) {
+  const int64_t items = (int64_t)plan.blocks * plan.splits;
+  const int grid = (int)std::min<int64_t>(items, BM == 64 ? 512 : 1024);
+  auto kern = !ta ? (!tb ? dd_gemm_failed<BM, RM, XM, false, false, SPLIT>
+                         : dd_gemm_failed<BM, RM, XM, false, true, SPLIT>)
+                  : (!tb ? dd_gemm_failed<BM, RM, XM, true, false, SPLIT>
+                         : dd_gemm_failed<BM, RM, XM, true, true, SPLIT>);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, p, failed, plan.blocks, plan.splits,
+                     whole);
+  return hipGetLastError();
+}
+
+template <bool SPLIT>
+static hipError_t launch_failed(const GemmParams& p, bool ta, bool tb, const CrtFailed& failed,
+                                const FailedPlan& plan, uint8_t* whole, hipStream_t st) {
+  switch (plan.tile) {
+    case 4: return launch_failed_t<64, 4, true, SPLIT>(p, ta, tb, failed, plan, whole, st);
+    case 2: return launch_failed_t<32, 2, false, SPLIT>(p, ta, tb, failed, plan, whole, st);
+    case KS_TILE:
+      return launch_failed_t<KS_B, KS_R, false, SPLIT>(p, ta, tb, failed, plan, whole, st);
+  }
+  return hipErrorInvalidValue;                   // (timed_plan takes no other)
+}
+
+hipError_t launch_gemm_failed(const GemmParams& q, bool ta, bool tb, const CrtFailed& failed,
+                              const FailedPlan& plan, void* scratch, hipStream_t st) {
+  GemmParams p = q;
+  p.tiles_m = plan.tiles_m;
+  p.tiles_n = plan.tiles_n;
+  p.kchunk = plan.kchunk;
+  if (plan.splits == 1) return launch_failed<false>(p, ta, tb, failed, plan, nullptr, st);
+  p.w_hi = (double*)((char*)scratch + plan.flag_bytes);
+  p.w_lo = p.w_hi + (size_t)plan.splits * p.m * p.n;
+  uint8_t* whole = (uint8_t*)scratch;
+  const hipError_t e = launch_failed<true>(p, ta, tb, failed, plan, whole, st);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)(((p.m + 3) / 4 * p.n + 255) / 256)), block(256);
+  auto kern = plan.splits == 2    ? dd_failed_reduce<2>
+              : plan.splits == 4  ? dd_failed_reduce<4>
+              : plan.splits == 8  ? dd_failed_reduce<8>
+              : plan.splits == 16 ? dd_failed_reduce<16>
+                                  : dd_failed_reduce<32>;
+  hipLaunchKernelGGL(kern, grid, block, 0, st, p, failed, tile_info(plan.tile)->bm, whole);
+  return hipGetLastError();
+}
+
 // Add the S k-split partials of every entry in a fixed order and apply the
 // alpha / beta update.  One thread per entry: partial s of consecutive
-// entries is one coalesced load per wave, and the S partials (S a power of
-// two) are summed in a balanced pairwise tree -- ((p0 + p1) + (p2 + p3)) +
-// ... -- by a carry-save stack of at most six pending sums: the sum of the
-// partials seen so far is held as sums over runs of 2^j partials, and a new
-// run is merged with the pending one of its size before it is pushed (the
-// earlier run always the left operand).  The order does not depend on the
-// schedule, so the result is deterministic.  S is a template parameter, so
-// the loop unrolls and the stack stays in registers.
+// entries is one coalesced load per wave.
 template <int S>
 __global__ void __launch_bounds__(256) dd_splitk_reduce(GemmParams p) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -795,22 +916,10 @@ __global__ void __launch_bounds__(256) dd_splitk_reduce(GemmParams p) {
   const int64_t i = e % p.m, j = e / p.m;
   if (p.tri == 1 && i > j) return;
   if (p.tri == 2 && i < j) return;
-  ddv st[7];
-  int depth = 0;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    ddv v{p.w_hi[(int64_t)s * total + e], p.w_lo[(int64_t)s * total + e]};
-    // partial s closes a run of 2^t partials for every trailing one bit t of s + 1
-#pragma unroll
-    for (int t = s + 1; (t & 1) == 0; t >>= 1) v = dd_add(st[--depth], v);
-    st[depth++] = v;
-  }
-  const ddv v = st[0];
-  ddv r = dd_mul(ddv{p.alpha_hi, p.alpha_lo}, v);
-  const int64_t ci = i + j * p.ldc;
-  if (!p.beta_zero) r = dd_add(r, dd_mul(ddv{p.beta_hi, p.beta_lo}, c_input(p, i, j)));
-  p.c_hi[ci] = r.hi;
-  p.c_lo[ci] = r.lo;
+  store_entry(p, i, j, split_sum<S>([&](int q) {
+                const int64_t at = (int64_t)q * total + e;
+                return ddv{p.w_hi[at], p.w_lo[at]};
+              }));
 }
 
 // C <- beta * C on the whole matrix (tri 0) or one triangle; beta = 0 writes
@@ -871,11 +980,6 @@ hipError_t launch_join_pairs(const double* hi, const double* lo, double* pairs, 
   X(2, 32, 32, 16, 2, 2, 0)   \
   X(3, 128, 64, 8, 8, 4, 0)   \
   X(4, 64, 64, 16, 4, 4, 1)
-
-// Entry 5, the small tile: 16 x 16, its four waves sharing the terms of every
-// 32-deep k-tile (dd_ksplit_mainloop).  The accurate form, whose sums run in
-// the order of the terms, has its own kernel of one entry per thread.
-constexpr int KS_TILE = 5, KS_B = 16, KS_BKG = 8, KS_R = 2, KS_KW = 4;
 
 static const TileInfo kTiles[] = {
 #define X(id, bm, bn, bk, rm, rn, xm) {bm, bn, bk, (bm / rm) * (bn / rn)},
@@ -943,15 +1047,7 @@ hipError_t launch_gemm(int tile, const GemmParams& p, bool ta, bool tb, bool acc
                        int splitk, hipStream_t st) {
   const TileInfo* t = tile_info(tile);
   if (!t) return hipErrorInvalidValue;
-  int nblocks;
-  if (p.tri == 0) {
-    nblocks = p.tiles_m * p.tiles_n;
-  } else if ((p.tiles_m & 7) == 0) {           // 8 x 8 blocks over the triangle
-    const int s8 = p.tiles_m >> 3;
-    nblocks = 64 * (s8 * (s8 + 1) / 2);
-  } else {
-    nblocks = p.tiles_m * (p.tiles_m + 1) / 2;
-  }
+  const int nblocks = tile_blocks(p.tri, p.tiles_m, p.tiles_n);
   switch (tile) {
 #define X(id, bm, bn, bk, rm, rn, xm) \
   case id: return launch_ops<bm, bn, bk, rm, rn, xm != 0>(p, ta, tb, accurate, nblocks, splitk, st);

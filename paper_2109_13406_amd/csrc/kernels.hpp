@@ -61,10 +61,19 @@ struct CrtFailed {
   const uint8_t *block, *entry;
   int64_t ldf, lde;
 };
-// Failed entries of a tile above which it is computed whole.
-constexpr int CRT_FAILED_ENTRIES = 256;
+// How they are computed: tiles and k-ranges by the estimated time of all of C (if
+// much has failed, that is what is to be done), and the scratch of the ranges' sums
+// (flag_bytes for a flag a tile, then the sums; 0 if not split).  Split only
+// where that is estimated to save a fifth, since it takes a launch more, 4 us, in
+// every call: 1031 x 64 x 4001, but not 1024^3 or 8192 x 64 x 8192.
+struct FailedPlan {
+  int tile = 0, splits = 1, tiles_m = 0, tiles_n = 0, blocks = 0;
+  int64_t kchunk = 0;
+  size_t flag_bytes = 0, bytes = 0;
+};
+FailedPlan failed_plan(int tri, int64_t m, int64_t n, int64_t k);
 hipError_t launch_gemm_failed(const GemmParams& p, bool ta, bool tb, const CrtFailed& failed,
-                              hipStream_t st);
+                              const FailedPlan& plan, void* scratch, hipStream_t st);
 hipError_t launch_splitk_reduce(const GemmParams& p, int splitk, hipStream_t st);
 // Persistent grouped kernel over the `which`-th item list: counts[c] items per
 // tile shape, lists stored back to back starting at base + *items_offset

@@ -17,6 +17,7 @@
 #include <new>
 
 #include "../../include/mpdd.h"
+#include "../../include/mpdd_testing.h"
 #include "crt.hpp"
 #include "kernels.hpp"
 #include "scratch.hpp"
@@ -285,17 +286,7 @@ int run_plain(mpdd_handle h, const mpdd_opts* o, bool ta, bool tb, int tri, int6
   // (the result is then that of the same call with opts->splitk = S)
   if (fixed && !(o && o->splitk > 0))
     while (S > 1 && partial_bytes(S) > (double)fixed->bytes) S >>= 1;
-  // k-range per slice: a whole number of staged k-tiles
-  int64_t chunk = (k + S - 1) / S;
-  chunk = (chunk + t->bk - 1) / t->bk * t->bk;
-  while (S > 1 && (int64_t)(S - 1) * chunk >= k) S >>= 1;   // no empty slices
-  if (S > 1) {
-    chunk = (k + S - 1) / S;
-    chunk = (chunk + t->bk - 1) / t->bk * t->bk;
-  } else {
-    chunk = k;
-  }
-  p.kchunk = chunk;
+  p.kchunk = split_chunk(k, t->bk, S);
 
   if (S == 1) return hip_status(launch_gemm(pl.tile, p, ta, tb, accurate, 1, st));
 
@@ -477,6 +468,16 @@ int mpdd_ozaki_split(mpdd_handle h, int algo, const char* trans, mpdd_int rows, 
   if (!exps || !slices || (k > 0 && (!X_hi || !X_lo))) return MPDD_ERR_ARG;
   return ozaki_split_entry(algo, !nt, rows, k, X_hi, X_lo, ld, nslices, wf, w, exps, slices, ldq,
                            rows_p, (hipStream_t)stream, h->scratch);
+}
+
+int mpdd_test_route(int op, mpdd_int m, mpdd_int n, mpdd_int k, int* tile, int* splitk) {
+  const bool tri = op == MPDD_OP_SYRK;
+  const TilePlan plan = default_plan(m, n, k, tri, 32);
+  if (tile) *tile = plan.tile;
+  if (splitk) *splitk = plan.splitk;
+  if (op == MPDD_TEST_CGEMM && complex_route(m, n, k)) return 1;
+  if (op == MPDD_TEST_QGEMM) return qd_guarded_shape(m, n, k) ? 1 : 0;
+  return (int)default_route(tri, m, n, k);
 }
 
 int mpdd_create(mpdd_handle* h, const char* tuner_cache_path) {

@@ -2596,7 +2596,9 @@ static int ozaki_crt_gemm(const mpdd_opts* opts, bool guarded, int tri, bool ta,
   const size_t e_bytes = round_up((m + n) * sizeof(int), 256);
   const size_t pa_bytes = crt_part_bytes(m), pb_bytes = tri ? 0 : crt_part_bytes(n);
   const size_t g_bytes = guarded ? crt_guard_bytes(mp, np) : 0;
-  const size_t total = qa_bytes + qb_bytes + x_bytes + e_bytes + pa_bytes + pb_bytes + g_bytes;
+  const FailedPlan plan = guarded ? failed_plan(tri, m, n, k) : FailedPlan();
+  const size_t total = qa_bytes + qb_bytes + x_bytes + e_bytes + pa_bytes + pb_bytes + g_bytes +
+                       plan.bytes;
   if (guarded && total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
   if (pool.get(&ws, total, st) != hipSuccess) {
@@ -2628,7 +2630,7 @@ static int ozaki_crt_gemm(const mpdd_opts* opts, bool guarded, int tri, bool ta,
   guard.plane = -1;
   float coef = 0.0f;
   if (guarded) {
-    guard = crt_guard_at(at, mp, np, A, B);
+    guard = crt_guard_at(take(g_bytes), mp, np, A, B);
     guard.plane = count;
     if (tri) {                    // op(B)'s columns are op(A)'s rows
       guard.tb = guard.ta;
@@ -2653,7 +2655,8 @@ static int ozaki_crt_gemm(const mpdd_opts* opts, bool guarded, int tri, bool ta,
     g.c_hi = c_hi; g.c_lo = c_lo; g.ldc = ldc;
     g.tri = tri;
     g.beta_zero = beta_zero;
-    e = launch_gemm_failed(g, ta, tb, CrtFailed{guard.block, guard.entry, guard.ldf, mp}, st);
+    e = launch_gemm_failed(g, ta, tb, CrtFailed{guard.block, guard.entry, guard.ldf, mp}, plan,
+                           take(plan.bytes), st);
   }
   const hipError_t ef = pool.put(ws, st);
   if (e != hipSuccess || ef != hipSuccess) return MPDD_ERR_HIP;
@@ -2741,8 +2744,10 @@ int ozaki_guarded_long_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, d
   const size_t mag_bytes = round_up((size_t)parts * mp * np * 4, 256);
   const size_t e_bytes = round_up((m + n) * sizeof(int), 256);
   const size_t px_bytes = crt_part_bytes(xr), py_bytes = crt_part_bytes(yr);
-  const size_t total = y_bytes + x_bytes + mag_bytes + e_bytes + px_bytes + py_bytes +
-                       crt_guard_bytes(mp, np);
+  const size_t g_bytes = crt_guard_bytes(mp, np);
+  const FailedPlan plan = failed_plan(0, m, n, k);
+  const size_t total = y_bytes + x_bytes + mag_bytes + e_bytes + px_bytes + py_bytes + g_bytes +
+                       plan.bytes;
   if (total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
   if (pool.get(&ws, total, st) != hipSuccess) {
@@ -2773,7 +2778,7 @@ int ozaki_guarded_long_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, d
   B.exps = A.exps + m;
   crt_set_parts(X, take(px_bytes));
   crt_set_parts(Y, take(py_bytes));
-  const CrtGuard guard = crt_guard_at(at, mp, np, A, B);
+  const CrtGuard guard = crt_guard_at(take(g_bytes), mp, np, A, B);
   q.block = guard.block;
   q.blocks = (int)((mp / 64) * (np / 64));
   launch_crt_scale(X, &Y, k, st);
@@ -2795,7 +2800,8 @@ int ozaki_guarded_long_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, d
     g.b_hi = b_hi; g.b_lo = b_lo; g.ldb = ldb;
     g.c_hi = c_hi; g.c_lo = c_lo; g.ldc = ldc;
     g.beta_zero = beta_zero;
-    e = launch_gemm_failed(g, ta, tb, CrtFailed{guard.block, guard.entry, guard.ldf, mp}, st);
+    e = launch_gemm_failed(g, ta, tb, CrtFailed{guard.block, guard.entry, guard.ldf, mp}, plan,
+                           take(plan.bytes), st);
   }
   const hipError_t ef = pool.put(ws, st);
   if (e != hipSuccess || ef != hipSuccess) return MPDD_ERR_HIP;
@@ -2829,8 +2835,9 @@ int ozaki_crt_cgemm(const void* opts_v, bool guarded, int opa, int opb, int64_t 
   const size_t x_bytes = (size_t)3 * count * mp * np;
   const size_t e_bytes = round_up((m + n) * sizeof(int), 256);
   const size_t g_bytes = guarded ? (size_t)16 * mp * np + crt_guard_bytes(mp, np) : 0;
+  const FailedPlan plan = guarded ? failed_plan(0, m, n, k) : FailedPlan();
   const size_t total = round_up(qa_bytes, 256) + round_up(qb_bytes, 256) + round_up(x_bytes, 256) +
-                       e_bytes + crt_part_bytes(m) + crt_part_bytes(n) + g_bytes;
+                       e_bytes + crt_part_bytes(m) + crt_part_bytes(n) + g_bytes + plan.bytes;
   if (guarded && total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
   if (pool.get(&ws, total, st) != hipSuccess) {
@@ -2912,7 +2919,8 @@ int ozaki_crt_cgemm(const void* opts_v, bool guarded, int opa, int opb, int64_t 
       g.b_hi = bh[q]; g.b_lo = bl[q]; g.ldb = ldb;
       g.c_hi = q < 2 ? prh : pih; g.c_lo = q < 2 ? prl : pil; g.ldc = m;
       e = launch_gemm_failed(g, opa != 0, opb != 0,
-                             CrtFailed{guard.block, guard.entry, guard.ldf, mp}, st);
+                             CrtFailed{guard.block, guard.entry, guard.ldf, mp}, plan,
+                             (char*)ws + (total - plan.bytes), st);
     }
   }
   const hipError_t ef = pool.put(ws, st);

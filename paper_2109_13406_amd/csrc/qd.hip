@@ -150,6 +150,9 @@ __device__ __forceinline__ void qd_add(qacc& c, const qacc& o) {
   qd_renorm(c);
 }
 
+// Failed entries of a tile above which it is computed whole.
+constexpr int QD_FAILED_ENTRIES = 256;
+
 // The entries of C that a guarded modular product left to the plain one, as
 // dd_gemm_failed, in units of one 32 x 32 tile.
 template <bool TA, bool TB>
@@ -157,7 +160,7 @@ __global__ void __launch_bounds__(256)
 qd_gemm_failed(QgemmParams p, CrtFailed failed, int tiles_m, int tiles_n) {
   __shared__ QdTileSmem sm;
   __shared__ unsigned char set[256];
-  __shared__ short list[CRT_FAILED_ENTRIES];
+  __shared__ short list[QD_FAILED_ENTRIES];
   __shared__ int number;
   const int tiles = tiles_m * tiles_n, stride = (int)gridDim.x;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -180,11 +183,11 @@ qd_gemm_failed(QgemmParams p, CrtFailed failed, int tiles_m, int tiles_n) {
       for (int e = tid; e < 1024; e += 256)
         if (wanted(i0 + e % 32, j0 + e / 32)) {
           const int at = atomicAdd(&number, 1);
-          if (at < CRT_FAILED_ENTRIES) list[at] = (short)e;
+          if (at < QD_FAILED_ENTRIES) list[at] = (short)e;
         }
       __syncthreads();
       const int count = number;
-      if (count > CRT_FAILED_ENTRIES) {
+      if (count > QD_FAILED_ENTRIES) {
         qd_tile<TA, TB>(p, i0, j0, sm, wanted);
       } else {
         for (int w = wave; w < count; w += 4) {

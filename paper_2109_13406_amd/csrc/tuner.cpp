@@ -117,6 +117,10 @@ TilePlan default_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split) 
     const int s = std::min(max_split, default_split(tiles, k, tri));
     return TilePlan{4, s, plan_time(kTileTimes[2], m, n, k, tri, s)};
   }
+  return timed_plan(m, n, k, tri, max_split);
+}
+
+TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split) {
   TilePlan best{2, 1, 0.0};
   for (const TileTime& t : kTileTimes)
     for (int s = 1; s <= max_split && (s == 1 || k / s >= 32); s *= 2) {
@@ -124,6 +128,13 @@ TilePlan default_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split) 
       if (best.us == 0.0 || us < best.us) best = TilePlan{t.tile, s, us};
     }
   return best;
+}
+
+int64_t split_chunk(int64_t k, int bk, int& splits) {
+  auto range = [&] { return ((k + splits - 1) / splits + bk - 1) / bk * bk; };
+  const int64_t asked = range();
+  while (splits > 1 && (int64_t)(splits - 1) * asked >= k) splits >>= 1;
+  return splits > 1 ? range() : k;
 }
 
 int default_tile(int64_t m, int64_t n, int64_t k, bool tri) {

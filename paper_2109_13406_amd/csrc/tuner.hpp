@@ -45,7 +45,14 @@ struct TilePlan {
 };
 int default_split(int64_t tiles, int64_t k, bool tri);   // k-split of a named tile
 TilePlan default_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split);
+// (by the time alone, of the square tiles with splits up to max_split)
+TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split);
 int default_tile(int64_t m, int64_t n, int64_t k, bool tri);
+
+// The k-range of each of `splits` slices of a product, a whole number of staged
+// k-tiles of depth bk (splits is halved where the ranges asked for leave slices
+// empty).
+int64_t split_chunk(int64_t k, int bk, int& splits);
 
 }  // namespace mpdd
 
