@@ -693,21 +693,27 @@ dd_grouped_ksplit(const char* __restrict__ base, const ServeReq* __restrict__ re
 }
 
 // The entries of C that a guarded modular product (ozaki.hip) left to the
-// plain one, in units of a FailedPlan's tiles and k-ranges.  A fixed grid looks
-// through the bytes of the tiles' 64 x 64 blocks, each workgroup at the items
-// (tile, k-range) blockIdx.x, + gridDim.x, ... 256 at a time (one per thread).  A
-// tile with many failed entries is computed whole, by the steps of
+// plain one, in units of a FailedPlan's tiles and k-ranges: a workgroup looks at
+// the byte of the 64 x 64 block of its tile.  (Of small tiles, of up to 256 at a
+// time, 1024 workgroups in all; large ones are too unequal for that: 512 workgroups
+// for 4096^2 took twice as long where the failed ones lie in a triangle.)  A tile with many failed entries is computed whole, by the steps of
 // dd_gemm_kernel, and those entries stored (SPLIT: its partial sums, and
 // dd_failed_reduce adds them); with few, each wave takes entries of its own
 // (SPLIT: a tile's workgroups share them): lanes take every 64th term with the
-// accurate dd steps and meet in a fixed order.  At k = 512 an entry costs a wave
+// accurate dd steps and meet in a fixed order.  A tile that is not 64 x 64 is summed
+// in `parts` ranges, as many as the plain product's k-split, whose shorter
+// sums round less (twice as many for that of 64 x 64 tiles, which round a little
+// less by themselves).  1024^3, rows of one dominant entry: 0.57 units of 2^-104
+// |A||B| in root mean square by the plain product (split in four), 1.34 in one range,
+// 0.67 in four, 0.47 in eight.  At k = 512 an entry costs a wave
 // about 3 us, a tile of 64 x 64 its workgroup 170 to 230 us, of 32 x 32 49 to 64,
 // of 16 x 16 15 to 22, hence FEW (and at least a row and a column of the tile: the
 // accurate steps take unnormalised pairs too).  Usually there are none, and the
 // launch is one load per tile: 4 us.
 template <int BM, int RM, bool XM, bool TA, bool TB, bool SPLIT>
-__global__ void __launch_bounds__(256, BM == 64 ? 2 : BM == 32 ? 4 : 3)
-dd_gemm_failed(GemmParams args, CrtFailed failed, int blocks, int splits, uint8_t* whole) {
+__global__ void __launch_bounds__(256, BM == 64 ? 2 : 3)
+dd_gemm_failed(GemmParams args, CrtFailed failed, int blocks, int splits, int parts,
+               uint8_t* whole) {
   constexpr int SUB = 64 / BM;                   // tiles per block edge
   constexpr bool KS = BM == KS_B;
   constexpr int FEW = KS ? 32 : BM == 32 ? 72 : 256;
@@ -730,11 +736,14 @@ dd_gemm_failed(GemmParams args, CrtFailed failed, int blocks, int splits, uint8_
     for (int q = 0; q < nq; ++q) {
       const int state = set[q];
       if (state == 0) continue;                  // (the same for every thread)
+      GemmParams p = args;
       // (opaque, so that the addresses made of them are not kept in registers
       // around the loops: the tile's steps need those)
-      GemmParams p = args;
-      asm volatile("" : "+s"(p.a_hi), "+s"(p.a_lo), "+s"(p.b_hi), "+s"(p.b_lo), "+s"(p.lda),
-                        "+s"(p.ldb), "+s"(p.k));
+      auto opaque = [&] {
+        asm volatile("" : "+s"(p.a_hi), "+s"(p.a_lo), "+s"(p.b_hi), "+s"(p.b_lo), "+s"(p.lda),
+                          "+s"(p.ldb), "+s"(p.k));
+      };
+      opaque();
       const int item = base + q * stride, z = SPLIT ? item / blocks : 0;
       (void)tile_coords(p, SPLIT ? item % blocks : item, blocks, bi, bj);
       const int64_t i0 = (int64_t)bi * BM, j0 = (int64_t)bj * BM;
@@ -757,15 +766,35 @@ dd_gemm_failed(GemmParams args, CrtFailed failed, int blocks, int splits, uint8_
       const bool all = state == 2 || number > FEW;
       if (SPLIT && z == 0 && tid == 0) whole[bi + (int64_t)bj * p.tiles_m] = all;
       if (all) {
-        const int64_t kbeg = (int64_t)z * p.kchunk;
-        const int64_t kend = (SPLIT && kbeg + p.kchunk < p.k) ? kbeg + p.kchunk : p.k;
+        const int64_t kend = min((int64_t)(z + 1) * p.kchunk, p.k);
         double ch[RM][RM], cl[RM][RM];
-        if constexpr (KS)
-          dd_ksplit_mainloop<BM, BM, KS_BKG, RM, RM, KS_KW, TA, TB>(p, i0, j0, kbeg, kend, sm, ch,
-                                                                    cl);
-        else
-          dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(p, i0, j0, kbeg, kend, sm, ch,
-                                                                  cl);
+        if constexpr (XM) {
+          dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(
+              p, i0, j0, (int64_t)z * p.kchunk, kend, sm, ch, cl);
+        } else {
+          double sh[RM][RM] = {}, sl[RM][RM] = {};
+          const int64_t range = p.kchunk / parts;
+          for (int part = 0; part < parts; ++part) {
+            const int64_t kb = (int64_t)z * p.kchunk + part * range;
+            const int64_t ke = part + 1 < parts ? min(kb + range, kend) : kend;
+            opaque();
+            if constexpr (KS)
+              dd_ksplit_mainloop<BM, BM, KS_BKG, RM, RM, KS_KW, TA, TB>(p, i0, j0, kb, ke, sm, ch,
+                                                                        cl);
+            else
+              dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(p, i0, j0, kb, ke, sm, ch,
+                                                                      cl);
+#pragma unroll
+            for (int r = 0; r < RM; ++r)
+#pragma unroll
+              for (int c = 0; c < RM; ++c) {
+                const ddv v = dd_add(ddv{sh[r][c], sl[r][c]}, ddv{ch[r][c], cl[r][c]});
+                sh[r][c] = ch[r][c] = v.hi;
+                sl[r][c] = cl[r][c] = v.lo;
+              }
+            __syncthreads();                     // (the staging is free again)
+          }
+        }
         if (!KS || tid < (BM / RM) * (BM / RM))  // (the threads that hold the sums)
           dd_tile_epilogue<BM, BM, RM, RM, SPLIT>(p, i0, j0, z, ch, cl, wanted);
       } else {
@@ -839,14 +868,18 @@ static int tile_blocks(int tri, int tiles_m, int tiles_n) {
 }
 
 FailedPlan failed_plan(int tri, int64_t m, int64_t n, int64_t k) {
-  TilePlan t = timed_plan(m, n, k, tri != 0, 1);
-  const TilePlan split = timed_plan(m, n, k, tri != 0, 32);
+  const TilePlan whole = default_plan(m, n, k, tri != 0, 32);
+  const int plain = whole.splitk == 1 ? 1 : whole.splitk * (whole.tile == 4 ? 2 : 1);
+  const int edge = plain > 1 ? 32 : 64;          // (64 x 64 tiles: one range)
+  TilePlan t = timed_plan(m, n, k, tri != 0, 1, edge);
+  const TilePlan split = timed_plan(m, n, k, tri != 0, 32, edge);
   if (split.us < 0.8 * t.us) t = split;
   const TileInfo* info = tile_info(t.tile);
   FailedPlan f;
   f.tile = t.tile;
   f.splits = t.splitk;
   f.kchunk = split_chunk(k, info->bk, f.splits);
+  f.parts = std::max(1, plain / f.splits);
   f.tiles_m = (int)((m + info->bm - 1) / info->bm);
   f.tiles_n = (int)((n + info->bm - 1) / info->bm);
   f.blocks = tile_blocks(tri, f.tiles_m, f.tiles_n);
@@ -861,13 +894,13 @@ template <int BM, int RM, bool XM, bool SPLIT>
 static hipError_t launch_failed_t(const GemmParams& p, bool ta, bool tb, const CrtFailed& failed,
                                   const FailedPlan& plan, uint8_t* whole, hipStream_t st) {
   const int64_t items = (int64_t)plan.blocks * plan.splits;
-  const int grid = (int)std::min<int64_t>(items, BM == 64 ? 512 : 1024);
+  const int grid = (int)std::min<int64_t>(items, BM == 64 ? 1 << 16 : 1024);
   auto kern = !ta ? (!tb ? dd_gemm_failed<BM, RM, XM, false, false, SPLIT>
                          : dd_gemm_failed<BM, RM, XM, false, true, SPLIT>)
                   : (!tb ? dd_gemm_failed<BM, RM, XM, true, false, SPLIT>
                          : dd_gemm_failed<BM, RM, XM, true, true, SPLIT>);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, p, failed, plan.blocks, plan.splits,
-                     whole);
+                     plan.parts, whole);
   return hipGetLastError();
 }
 

@@ -65,9 +65,10 @@ struct CrtFailed {
 // much has failed, that is what is to be done), and the scratch of the ranges' sums
 // (flag_bytes for a flag a tile, then the sums; 0 if not split).  Split only
 // where that is estimated to save a fifth, since it takes a launch more, 4 us, in
-// every call: 1031 x 64 x 4001, but not 1024^3 or 8192 x 64 x 8192.
+// every call: 1031 x 64 x 4001, but not 1024^3 or 8192 x 64 x 8192.  parts: ranges
+// summed one after the other, where the plain product's k-split is finer.
 struct FailedPlan {
-  int tile = 0, splits = 1, tiles_m = 0, tiles_n = 0, blocks = 0;
+  int tile = 0, splits = 1, parts = 1, tiles_m = 0, tiles_n = 0, blocks = 0;
   int64_t kchunk = 0;
   size_t flag_bytes = 0, bytes = 0;
 };

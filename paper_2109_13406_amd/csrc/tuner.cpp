@@ -120,10 +120,10 @@ TilePlan default_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split) 
   return timed_plan(m, n, k, tri, max_split);
 }
 
-TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split) {
+TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split, int max_edge) {
   TilePlan best{2, 1, 0.0};
   for (const TileTime& t : kTileTimes)
-    for (int s = 1; s <= max_split && (s == 1 || k / s >= 32); s *= 2) {
+    for (int s = 1; t.edge <= max_edge && s <= max_split && (s == 1 || k / s >= 32); s *= 2) {
       const double us = plan_time(t, m, n, k, tri, s);
       if (best.us == 0.0 || us < best.us) best = TilePlan{t.tile, s, us};
     }

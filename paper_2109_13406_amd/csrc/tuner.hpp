@@ -45,8 +45,8 @@ struct TilePlan {
 };
 int default_split(int64_t tiles, int64_t k, bool tri);   // k-split of a named tile
 TilePlan default_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split);
-// (by the time alone, of the square tiles with splits up to max_split)
-TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split);
+// (by the time alone, of the square tiles up to max_edge with splits up to max_split)
+TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split, int max_edge = 64);
 int default_tile(int64_t m, int64_t n, int64_t k, bool tri);
 
 // The k-range of each of `splits` slices of a product, a whole number of staged

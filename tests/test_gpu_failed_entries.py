@@ -160,3 +160,46 @@ def test_failed_entries_cgemm(h, m, n, k, what):
         assert np.max(d / unit) <= 4 * (k + 8)          # two products a part
         assert np.array_equal(bits(G[q]), bits(G2[q]))
         assert np.array_equal(bits(G[q + 1]), bits(G2[q + 1]))
+
+
+def _exact_errors(A, B, got, rows, cols):
+    """Errors of got's sampled entries against the exact products, in units of
+    2^-104 (|A||B|)_ij: pairs as integers times 2^-S."""
+    S = 300
+    ints = lambda hi, lo: [int(h * 2.0 ** 200) * (1 << (S - 200)) + int(l * 2.0 ** 200) *
+                           (1 << (S - 200)) for h, l in zip(hi, lo)]
+    out = []
+    for i, j in zip(rows, cols):
+        a, b = ints(A[0][i], A[1][i]), ints(B[0][:, j], B[1][:, j])
+        exact = sum(x * y for x, y in zip(a, b))
+        size = sum(abs(x * y) for x, y in zip(a, b))
+        g = ints([got[0][i, j]], [got[1][i, j]])[0] << S
+        out.append((g - exact) * (1 << 104) / size)
+    return np.array(out)
+
+
+@pytest.mark.parametrize("m,n,k", [(1024, 1024, 1024), (600, 600, 600), (700, 200, 2000),
+                                   (1031, 64, 4001)])
+def test_refused_entries_round_no_more_than_the_plain_product(h, m, n, k):
+    """Rows of one dominant entry above many small ones: root mean square over 400
+    sampled entries, with 15 % for the sampling (three times the spread of the
+    ratio of two such means)."""
+    from paper_2109_13406_amd import binding as b
+    assert b.mpdd_test_route(b.MPDD_OP_GEMM, m, n, k)[0] > 0
+    case = W.gemm_case(7990, "N", "N", m, n, k, beta_zero=True)
+    case["alpha"] = (1.0, 0.0)
+    A = [W.view(x, m, k, case["lda"]) for x in case["A"]]
+    B = [W.view(x, k, n, case["ldb"]) for x in case["B"]]
+    # (sum |x| / 2^sigma < 4 and sum (x / 2^sigma)^2 < 2 for every row)
+    for v in A:
+        v *= 2.0 ** -np.ceil(np.log2(k / 2.0))
+    i = np.arange(m)
+    A[0][i, (7 * i) % k], A[1][i, (7 * i) % k] = 0.77, 0.77 * 2.0 ** -54
+    rng = np.random.default_rng(5)
+    rows, cols = rng.integers(0, m, 400), rng.integers(0, n, 400)
+    rms = []
+    for opts in (dict(algo=b.MPDD_PLAIN), None):
+        C = host(_call(h, case, {x: dev(case[x]) for x in "ABC"}, opts))
+        C = [W.view(x, m, n, case["ldc"]) for x in C]
+        rms.append(np.sqrt(np.mean(_exact_errors(A, B, C, rows, cols) ** 2)))
+    assert rms[1] <= 1.15 * rms[0], rms
