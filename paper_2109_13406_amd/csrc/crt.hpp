@@ -55,7 +55,8 @@ struct CrtOperand {
   const double *hi, *lo;
   const double* hi2;            // a second plane that counts for the row maxima, or null
   int64_t sr, sl, rows, rows_p; // rows_p: rows of a residue plane (padding included)
-  double *pmax, *psum;          // partial row maxima and sums [chunk][rows]
+  double *pmax, *psum, *pabs;   // partial row maxima, sums of squares and of magnitudes
+                                // [chunk][rows] (the sums are a guard's)
   int* exps;                    // row exponents
   int8_t* q;                    // residue planes
   double sign;
@@ -87,7 +88,8 @@ struct CrtGuard {
                                 // products, stored here as they are [4][np][mp]
   int check;                    // block is there already: skip tiles that failed whole
 };
-constexpr double CRT_GUARD_MIN_TERMS = 2.0;   // smallest sum (x / 2^sigma)^2 of a row
+constexpr double CRT_GUARD_MIN_TERMS = 2.0;   // smallest sum (x / 2^sigma)^2 of a row, or
+constexpr double CRT_GUARD_MIN_SUM = 4.0;     // smallest sum |x| / 2^sigma
 constexpr int CRT_GUARD_MAX_EXP = 400;        // largest |sigma|
 constexpr int CRT_GUARD_BITS = 109;           // narrowest grid of the guarded product
 

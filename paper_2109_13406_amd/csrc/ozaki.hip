@@ -112,9 +112,9 @@ oz_scale_rows_wave(const double* __restrict__ x, int64_t sr, int64_t sl, int64_t
   }
 }
 
-// Partial row maxima (and sums of squares) of both row operands of a modular
-// product in one launch: a workgroup takes 64 rows of one operand and one of
-// nch <= 16 chunks of l, and writes pmax[chunk][row] and psum[chunk][row];
+// Partial row maxima (and sums of squares and of magnitudes) of both row operands
+// of a modular product in one launch: a workgroup takes 64 rows of one operand and
+// one of nch <= 16 chunks of l, and writes pmax[chunk][row], psum and pabs;
 // the residue kernel reduces a row's chunks itself, so that no finishing
 // launch stands between them.  (At 2048^2 the two operands took 83 us in
 // three launches of 128, 512 and 8 workgroups.)  Rows contiguous across
@@ -124,7 +124,7 @@ constexpr int CRT_SCALE_CHUNKS = 16;
 
 __global__ void __launch_bounds__(256)
 oz_crt_scale(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int64_t chunk) {
-  __shared__ double red[2][4][64];
+  __shared__ double red[3][4][64];
   const bool first = (int)blockIdx.x < blocks_a;
   const CrtOperand& op = first ? opa : opb;
   const int64_t r0 = (int64_t)(first ? blockIdx.x : blockIdx.x - blocks_a) * 64;
@@ -138,9 +138,10 @@ oz_crt_scale(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int64_t ch
   if (r0 >= rows) return;                      // padding rows only
   double* __restrict__ pmax = op.pmax + (int64_t)blockIdx.y * rows;
   double* __restrict__ psum = op.psum + (int64_t)blockIdx.y * rows;
+  double* __restrict__ pabs = op.pabs + (int64_t)blockIdx.y * rows;
   if (sr == 1) {
     const int64_t r = (r0 + lane < rows) ? r0 + lane : rows - 1;
-    double mx = 0.0, sm = 0.0;
+    double mx = 0.0, sm = 0.0, ab = 0.0;
     int64_t l = l0 + wave;
     for (; l + 28 < l1; l += 32) {
       double v[8];
@@ -150,26 +151,31 @@ oz_crt_scale(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int64_t ch
       for (int u = 0; u < 8; ++u) {
         mx = fmax(mx, v[u]);
         sm = fma(v[u], v[u], sm);
+        ab += v[u];
       }
     }
     for (; l < l1; l += 4) {
       const double v = fabs(x[r + l * sl]);
       mx = fmax(mx, v);
       sm = fma(v, v, sm);
+      ab += v;
     }
     if (x2)
       for (l = l0 + wave; l < l1; l += 4) {
         const double v = fabs(x2[r + l * sl]);
         mx = fmax(mx, v);
         sm = fma(v, v, sm);
+        ab += v;
       }
     red[0][wave][lane] = mx;
     red[1][wave][lane] = sm;
+    red[2][wave][lane] = ab;
     __syncthreads();
     if (wave == 0 && r0 + lane < rows) {
       pmax[r0 + lane] = fmax(fmax(red[0][0][lane], red[0][1][lane]),
                              fmax(red[0][2][lane], red[0][3][lane]));
       psum[r0 + lane] = (red[1][0][lane] + red[1][1][lane]) + (red[1][2][lane] + red[1][3][lane]);
+      pabs[r0 + lane] = (red[2][0][lane] + red[2][1][lane]) + (red[2][2][lane] + red[2][3][lane]);
     }
     return;
   }
@@ -179,7 +185,7 @@ oz_crt_scale(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int64_t ch
     const int64_t rr = r0 + it * 16 + (tid >> 4);
     const int64_t r = rr < rows ? rr : rows - 1;
     const double* __restrict__ xr = x + r * sr;
-    double mx = 0.0, sm = 0.0;
+    double mx = 0.0, sm = 0.0, ab = 0.0;
     int64_t l = l0 + sub;
     for (; l + 48 < l1; l += 64) {
       double v[4];
@@ -189,27 +195,32 @@ oz_crt_scale(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int64_t ch
       for (int u = 0; u < 4; ++u) {
         mx = fmax(mx, v[u]);
         sm = fma(v[u], v[u], sm);
+        ab += v[u];
       }
     }
     for (; l < l1; l += 16) {
       const double v = fabs(xr[l]);
       mx = fmax(mx, v);
       sm = fma(v, v, sm);
+      ab += v;
     }
     if (x2)
       for (l = l0 + sub; l < l1; l += 16) {
         const double v = fabs(x2[r * sr + l]);
         mx = fmax(mx, v);
         sm = fma(v, v, sm);
+        ab += v;
       }
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       mx = fmax(mx, __shfl_xor(mx, off));
       sm += __shfl_xor(sm, off);
+      ab += __shfl_xor(ab, off);
     }
     if (sub == 0 && rr < rows) {
       pmax[rr] = mx;
       psum[rr] = sm;
+      pabs[rr] = ab;
     }
   }
 }
@@ -1381,15 +1392,24 @@ oz_combine_qd(const int32_t* __restrict__ x, int64_t mp, int64_t np, int nslices
 // magnitude digits floor(|x| 2^(7 - sigma_r)) in 0 .. 127; thr[r] the row's
 // share of the threshold, coef * Q with Q = (sum_l x_rl^2)^(1/2) 2^-sigma_r:
 // -inf for a zero or padding row (it is exact), NaN for a row that must not
-// take the modular route: Q^2 < CRT_GUARD_MIN_TERMS (a row of few terms, whose
-// plain products round less), non-finite entries, or an exponent near the
-// ends of the range.  bad[r] is set where a pair is not normalised.
+// take the modular route: a row of few terms, whose plain products round less,
+// non-finite entries, or an exponent near the ends of the range.  bad[r] is set
+// where a pair is not normalised.  A row of few terms has both Q^2 <
+// CRT_GUARD_MIN_TERMS and S = sum_l |x_rl| 2^-sigma_r < CRT_GUARD_MIN_SUM: one
+// with a large S beside a small Q^2 has S^2 / Q^2 > 8 terms' worth (as eight equal
+// ones), one of them dominant, as in Gram and Schur matrices and Cholesky
+// factors, and its entries pass or fail by their own bounds like any others.  (By
+// Q^2 alone every row of a Gram matrix was refused, 1024^3 490 us instead of 100.
+// Root mean square error of its product with a uniform one, and of its square, in
+// units of 2^-104 |A||B|: 0.010 and 0.026, plain product 0.14 and 0.21.)
 // KIND: 0 no guard, 1 guard, 2 guard of a complex product (the real or the
 // imaginary parts of an operand; Q over both, and the digits go to two planes).
-__device__ __forceinline__ float crt_threshold(double mx, double sum, int ex, float coef) {
+__device__ __forceinline__ float crt_threshold(double mx, double sum, double mags, int ex,
+                                               float coef) {
   if (mx == 0.0 && sum == 0.0) return -__builtin_inff();
   const double q2 = ldexp(sum, -2 * ex);
-  if (!(q2 >= CRT_GUARD_MIN_TERMS) || !(q2 <= 0x1p40) || ex > CRT_GUARD_MAX_EXP ||
+  const bool few = !(q2 >= CRT_GUARD_MIN_TERMS) && !(ldexp(mags, -ex) >= CRT_GUARD_MIN_SUM);
+  if (few || !(q2 <= 0x1p40) || ex > CRT_GUARD_MAX_EXP ||
       ex < -CRT_GUARD_MAX_EXP)
     return __builtin_nanf("");
   return (float)__builtin_sqrt(q2) * coef;
@@ -1420,10 +1440,14 @@ oz_crt_residues(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int nch
   const bool lanes_on_r = (sr == 1);
   const int row = tid >> 4;
   // this row's exponent (and magnitude sum), from its chunks' partial values
-  double mx = 0.0, sum = 0.0;
+  double mx = 0.0, sum = 0.0, mags = 0.0;
   if (r0 + row < rows && (tid & 15) < nch) {
-    mx = op.pmax[(int64_t)(tid & 15) * rows + r0 + row];
-    if (GUARD) sum = op.psum[(int64_t)(tid & 15) * rows + r0 + row];
+    const int64_t at = (int64_t)(tid & 15) * rows + r0 + row;
+    mx = op.pmax[at];
+    if (GUARD) {
+      sum = op.psum[at];
+      mags = op.pabs[at];
+    }
   }
   {
     // entry e of the block: lanes on r, 32 consecutive rows per half-wave;
@@ -1444,7 +1468,10 @@ oz_crt_residues(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int nch
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       mx = fmax(mx, __shfl_xor(mx, off));
-      if (GUARD) sum += __shfl_xor(sum, off);
+      if (GUARD) {
+        sum += __shfl_xor(sum, off);
+        mags += __shfl_xor(mags, off);
+      }
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half)
@@ -1460,7 +1487,7 @@ oz_crt_residues(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int nch
   if (mx != 0.0) frexp(mx, &ex);
   if (l0 == 0 && (tid & 15) == 0) {
     if (r0 + row < rows) op.exps[r0 + row] = ex;
-    if (GUARD) op.thr[r0 + row] = crt_threshold(mx, sum, ex, coef);
+    if (GUARD) op.thr[r0 + row] = crt_threshold(mx, sum, mags, ex, coef);
   }
   __syncthreads();
   const int lq = (tid & 15) * 8;
@@ -1802,15 +1829,18 @@ oz_crt_long(CrtOperand op, CrtLong q) {
   if (tid < 512) {
     // the rows' exponents and thresholds from their chunks' partial values
     const int row = tid >> 4;
-    double mx = 0.0, sum = 0.0;
+    double mx = 0.0, sum = 0.0, mags = 0.0;
     if (r0 + row < op.rows && (tid & 15) < q.nch) {
-      mx = op.pmax[(int64_t)(tid & 15) * op.rows + r0 + row];
-      sum = op.psum[(int64_t)(tid & 15) * op.rows + r0 + row];
+      const int64_t at = (int64_t)(tid & 15) * op.rows + r0 + row;
+      mx = op.pmax[at];
+      sum = op.psum[at];
+      mags = op.pabs[at];
     }
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       mx = fmax(mx, __shfl_xor(mx, off));
       sum += __shfl_xor(sum, off);
+      mags += __shfl_xor(mags, off);
     }
     int ex = 0;
     if (mx != 0.0) frexp(mx, &ex);
@@ -1818,7 +1848,7 @@ oz_crt_long(CrtOperand op, CrtLong q) {
       rowexp[row] = ex;
       if (cb == 0 && split == 0) {
         if (r0 + row < op.rows) op.exps[r0 + row] = ex;
-        op.thr[r0 + row] = crt_threshold(mx, sum, ex, q.coef);
+        op.thr[r0 + row] = crt_threshold(mx, sum, mags, ex, q.coef);
       }
     }
   }
@@ -2135,21 +2165,28 @@ oz_crt_residues_qd(CrtQdOperand opa, CrtQdOperand opb, int blocks_a, int64_t k, 
   const bool lanes_on_r = (sr == 1);
   const int row = tid >> 4, lq = (tid & 15) * 4;
   // the row's exponent from its chunks' partial maxima, as in oz_crt_residues
-  double mx = 0.0, sum = 0.0;
+  double mx = 0.0, sum = 0.0, mags = 0.0;
   if (r0 + row < rows && (tid & 15) < nch) {
-    mx = op.s.pmax[(int64_t)(tid & 15) * rows + r0 + row];
-    if (GUARD) sum = op.s.psum[(int64_t)(tid & 15) * rows + r0 + row];
+    const int64_t at = (int64_t)(tid & 15) * rows + r0 + row;
+    mx = op.s.pmax[at];
+    if (GUARD) {
+      sum = op.s.psum[at];
+      mags = op.s.pabs[at];
+    }
   }
 #pragma unroll
   for (int off = 1; off < 16; off <<= 1) {
     mx = fmax(mx, __shfl_xor(mx, off));
-    if (GUARD) sum += __shfl_xor(sum, off);
+    if (GUARD) {
+      sum += __shfl_xor(sum, off);
+      mags += __shfl_xor(mags, off);
+    }
   }
   int ex = 0;
   if (mx != 0.0) frexp(mx, &ex);
   if (l0 == 0 && (tid & 15) == 0) {
     if (r0 + row < rows) op.s.exps[r0 + row] = ex;
-    if (GUARD) op.s.thr[r0 + row] = crt_threshold(mx, sum, ex, coef);
+    if (GUARD) op.s.thr[r0 + row] = crt_threshold(mx, sum, mags, ex, coef);
   }
   const int sh = CRT_QD_GRID_BITS - ex;
   uint32_t mag = 0u;
@@ -2485,18 +2522,19 @@ static void launch_crt_products(const CrtTiling& tl, const int8_t* qa, const int
 }
 
 // Chunks of l of the partial row maxima, and the bytes of one operand's
-// partials (maxima, then sums).
+// partials (maxima, then both sums).
 static int64_t crt_chunks(int64_t k) {
   return std::min<int64_t>(CRT_SCALE_CHUNKS, std::max<int64_t>(1, (k + 63) / 64));
 }
 
 static size_t crt_part_bytes(int64_t rows) {
-  return (size_t)round_up(2 * CRT_SCALE_CHUNKS * rows * (int64_t)sizeof(double), 256);
+  return (size_t)round_up(3 * CRT_SCALE_CHUNKS * rows * (int64_t)sizeof(double), 256);
 }
 
 static void crt_set_parts(CrtOperand& op, void* part) {
   op.pmax = (double*)part;
   op.psum = op.pmax + CRT_SCALE_CHUNKS * op.rows;
+  op.pabs = op.psum + CRT_SCALE_CHUNKS * op.rows;
 }
 
 // Partial row maxima of one operand or (b non-null) of both.
