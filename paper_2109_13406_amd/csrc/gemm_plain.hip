@@ -693,143 +693,121 @@ dd_grouped_ksplit(const char* __restrict__ base, const ServeReq* __restrict__ re
 }
 
 // The entries of C that a guarded modular product (ozaki.hip) left to the
-// plain one, in units of a FailedPlan's tiles and k-ranges: a workgroup looks at
-// the byte of the 64 x 64 block of its tile.  (Of small tiles, of up to 256 at a
-// time, 1024 workgroups in all; large ones are too unequal for that: 512 workgroups
-// for 4096^2 took twice as long where the failed ones lie in a triangle.)  A tile with many failed entries is computed whole, by the steps of
-// dd_gemm_kernel, and those entries stored (SPLIT: its partial sums, and
-// dd_failed_reduce adds them); with few, each wave takes entries of its own
-// (SPLIT: a tile's workgroups share them): lanes take every 64th term with the
-// accurate dd steps and meet in a fixed order.  A tile that is not 64 x 64 is summed
-// in `parts` ranges, as many as the plain product's k-split, whose shorter
-// sums round less (twice as many for that of 64 x 64 tiles, which round a little
-// less by themselves).  1024^3, rows of one dominant entry: 0.57 units of 2^-104
-// |A||B| in root mean square by the plain product (split in four), 1.34 in one range,
-// 0.67 in four, 0.47 in eight.  At k = 512 an entry costs a wave
-// about 3 us, a tile of 64 x 64 its workgroup 170 to 230 us, of 32 x 32 49 to 64,
+// plain one, in units of a FailedPlan's tiles and k-ranges, one a workgroup, which
+// ends at once if its tile's 64 x 64 block has none.  (No workgroup walks several
+// tiles: the loops around them cost the tile's steps their registers, and failed
+// tiles in a triangle left the walks twice as unequal.)  A tile with many failed
+// entries is computed whole, by the steps of dd_gemm_kernel, and those entries
+// stored (SPLIT: its partial sums, and dd_failed_reduce adds them); with few, each
+// wave takes entries of its own (SPLIT: a tile's workgroups share them): lanes take
+// every 64th term with the accurate dd steps and meet in a fixed order.  A tile that
+// is not 64 x 64 is summed in `parts` ranges, as many as the plain product's
+// k-split, whose shorter sums round less (twice as many for that of 64 x 64 tiles,
+// which round a little less by themselves).  1024^3, rows of one dominant entry:
+// 0.57 units of 2^-104 |A||B| in root mean square by the plain product (split in
+// four), 1.34 in one range, 0.67 in four, 0.47 in eight.  At k = 512 an entry costs a
+// wave about 3 us, a tile of 64 x 64 its workgroup 170 to 230 us, of 32 x 32 49 to 64,
 // of 16 x 16 15 to 22, hence FEW (and at least a row and a column of the tile: the
 // accurate steps take unnormalised pairs too).  Usually there are none, and the
 // launch is one load per tile: 4 us.
 template <int BM, int RM, bool XM, bool TA, bool TB, bool SPLIT>
 __global__ void __launch_bounds__(256, BM == 64 ? 2 : 3)
-dd_gemm_failed(GemmParams args, CrtFailed failed, int blocks, int splits, int parts,
+dd_gemm_failed(GemmParams p, CrtFailed failed, int blocks, int splits, int parts,
                uint8_t* whole) {
   constexpr int SUB = 64 / BM;                   // tiles per block edge
   constexpr bool KS = BM == KS_B;
   constexpr int FEW = KS ? 32 : BM == 32 ? 72 : 256;
   constexpr int U = BM == 64 ? 4 : 2;
   __shared__ std::conditional_t<KS, KSplitSmem<BM, BM, KS_BKG * KS_KW>, DDTileSmem<BM, BM, 16>> sm;
-  __shared__ unsigned char set[256];
   __shared__ short list[FEW];
   __shared__ int number, mine;
-  const int items = blocks * splits, stride = (int)gridDim.x;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int base = blockIdx.x; base < items; base += 256 * stride) {
-    const int t = base + tid * stride;
-    int n = 0, bi, bj;
-    // (blocks outside a triangle have no byte)
-    if (t < items && tile_coords(args, SPLIT ? t % blocks : t, blocks, bi, bj))
-      n = failed.block[(int64_t)(bj / SUB) * failed.ldf + bi / SUB];
-    set[tid] = (unsigned char)n;
-    if (__syncthreads_count(n) == 0) continue;
-    const int nq = min(256, (items - base + stride - 1) / stride);
-    for (int q = 0; q < nq; ++q) {
-      const int state = set[q];
-      if (state == 0) continue;                  // (the same for every thread)
-      GemmParams p = args;
-      // (opaque, so that the addresses made of them are not kept in registers
-      // around the loops: the tile's steps need those)
-      auto opaque = [&] {
-        asm volatile("" : "+s"(p.a_hi), "+s"(p.a_lo), "+s"(p.b_hi), "+s"(p.b_lo), "+s"(p.lda),
-                          "+s"(p.ldb), "+s"(p.k));
-      };
-      opaque();
-      const int item = base + q * stride, z = SPLIT ? item / blocks : 0;
-      (void)tile_coords(p, SPLIT ? item % blocks : item, blocks, bi, bj);
-      const int64_t i0 = (int64_t)bi * BM, j0 = (int64_t)bj * BM;
-      auto wanted = [&](int64_t i, int64_t j) {
-        return i < p.m && j < p.n && !(p.tri == 1 && i > j) && !(p.tri == 2 && i < j) &&
-               failed.entry[j * failed.lde + i] != 0;
-      };
-      if (tid == 0) number = mine = 0;
-      __syncthreads();
-      if (state != 2) {
-        for (int e = tid; e < BM * BM; e += 256)
-          if (wanted(i0 + e % BM, j0 + e / BM)) {
-            atomicAdd(&number, 1);
-            if (SPLIT && (e % BM + e / BM) % splits != z) continue;     // another range's
-            const int at = atomicAdd(&mine, 1);
-            if (at < FEW) list[at] = (short)e;
-          }
-        __syncthreads();
+  const int z = SPLIT ? (int)blockIdx.x / blocks : 0;
+  int bi, bj;
+  if (!tile_coords(p, SPLIT ? (int)blockIdx.x % blocks : (int)blockIdx.x, blocks, bi, bj)) return;
+  const int state = failed.block[(int64_t)(bj / SUB) * failed.ldf + bi / SUB];
+  if (state == 0) return;
+  const int64_t i0 = (int64_t)bi * BM, j0 = (int64_t)bj * BM;
+  auto wanted = [&](int64_t i, int64_t j) {
+    return i < p.m && j < p.n && !(p.tri == 1 && i > j) && !(p.tri == 2 && i < j) &&
+           failed.entry[j * failed.lde + i] != 0;
+  };
+  if (tid == 0) number = mine = 0;
+  __syncthreads();
+  if (state != 2) {
+    for (int e = tid; e < BM * BM; e += 256)
+      if (wanted(i0 + e % BM, j0 + e / BM)) {
+        atomicAdd(&number, 1);
+        if (SPLIT && (e % BM + e / BM) % splits != z) continue;     // another range's
+        const int at = atomicAdd(&mine, 1);
+        if (at < FEW) list[at] = (short)e;
       }
-      const bool all = state == 2 || number > FEW;
-      if (SPLIT && z == 0 && tid == 0) whole[bi + (int64_t)bj * p.tiles_m] = all;
-      if (all) {
-        const int64_t kend = min((int64_t)(z + 1) * p.kchunk, p.k);
-        double ch[RM][RM], cl[RM][RM];
-        if constexpr (XM) {
-          dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(
-              p, i0, j0, (int64_t)z * p.kchunk, kend, sm, ch, cl);
-        } else {
-          double sh[RM][RM] = {}, sl[RM][RM] = {};
-          const int64_t range = p.kchunk / parts;
-          for (int part = 0; part < parts; ++part) {
-            const int64_t kb = (int64_t)z * p.kchunk + part * range;
-            const int64_t ke = part + 1 < parts ? min(kb + range, kend) : kend;
-            opaque();
-            if constexpr (KS)
-              dd_ksplit_mainloop<BM, BM, KS_BKG, RM, RM, KS_KW, TA, TB>(p, i0, j0, kb, ke, sm, ch,
-                                                                        cl);
-            else
-              dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(p, i0, j0, kb, ke, sm, ch,
-                                                                      cl);
-#pragma unroll
-            for (int r = 0; r < RM; ++r)
-#pragma unroll
-              for (int c = 0; c < RM; ++c) {
-                const ddv v = dd_add(ddv{sh[r][c], sl[r][c]}, ddv{ch[r][c], cl[r][c]});
-                sh[r][c] = ch[r][c] = v.hi;
-                sl[r][c] = cl[r][c] = v.lo;
-              }
-            __syncthreads();                     // (the staging is free again)
-          }
-        }
-        if (!KS || tid < (BM / RM) * (BM / RM))  // (the threads that hold the sums)
-          dd_tile_epilogue<BM, BM, RM, RM, SPLIT>(p, i0, j0, z, ch, cl, wanted);
-      } else {
-        const int count = mine;
-        for (int w = wave; w < count; w += 4) {
-          const int64_t i = i0 + list[w] % BM, j = j0 + list[w] / BM;
-          ddv acc{0.0, 0.0};
-          auto term = [&](int64_t l, ddv& a, ddv& b) {
-            const int64_t oa = TA ? l + i * p.lda : i + l * p.lda;
-            const int64_t ob = TB ? j + l * p.ldb : l + j * p.ldb;
-            a = ddv{p.a_hi[oa], p.a_lo[oa]};
-            b = ddv{p.b_hi[ob], p.b_lo[ob]};
-          };
-          int64_t l = lane;
-          for (; l + 64 * (U - 1) < p.k; l += 64 * U) {     // U terms' loads at a time
-            ddv a[U], b[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) term(l + 64 * u, a[u], b[u]);
-#pragma unroll
-            for (int u = 0; u < U; ++u) acc = dd_add(acc, dd_mul(a[u], b[u]));
-          }
-          for (; l < p.k; l += 64) {
-            ddv a, b;
-            term(l, a, b);
-            acc = dd_add(acc, dd_mul(a, b));
-          }
-#pragma unroll
-          for (int off = 1; off < 64; off <<= 1)
-            acc = dd_add(acc, ddv{__shfl_xor(acc.hi, off), __shfl_xor(acc.lo, off)});
-          if (lane == 0) store_entry(p, i, j, acc);
-        }
-      }
-      __syncthreads();
-    }
     __syncthreads();
+  }
+  const bool all = state == 2 || number > FEW;
+  if (SPLIT && z == 0 && tid == 0) whole[bi + (int64_t)bj * p.tiles_m] = all;
+  if (all) {
+    const int64_t kend = min((int64_t)(z + 1) * p.kchunk, p.k);
+    double ch[RM][RM], cl[RM][RM];
+    if constexpr (XM) {
+      dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(
+          p, i0, j0, (int64_t)z * p.kchunk, kend, sm, ch, cl);
+    } else {
+      double sh[RM][RM] = {}, sl[RM][RM] = {};
+      const int64_t range = p.kchunk / parts;
+      for (int part = 0; part < parts; ++part) {
+        const int64_t kb = (int64_t)z * p.kchunk + part * range;
+        const int64_t ke = part + 1 < parts ? min(kb + range, kend) : kend;
+        // (opaque, so that the addresses made of them are not kept in registers
+        // around the loop: the tile's steps need those)
+        asm volatile("" : "+s"(p.a_hi), "+s"(p.a_lo), "+s"(p.b_hi), "+s"(p.b_lo), "+s"(p.lda),
+                          "+s"(p.ldb));
+        if constexpr (KS)
+          dd_ksplit_mainloop<BM, BM, KS_BKG, RM, RM, KS_KW, TA, TB>(p, i0, j0, kb, ke, sm, ch, cl);
+        else
+          dd_tile_mainloop<BM, BM, 16, RM, RM, TA, TB, false, XM>(p, i0, j0, kb, ke, sm, ch, cl);
+#pragma unroll
+        for (int r = 0; r < RM; ++r)
+#pragma unroll
+          for (int c = 0; c < RM; ++c) {
+            const ddv v = dd_add(ddv{sh[r][c], sl[r][c]}, ddv{ch[r][c], cl[r][c]});
+            sh[r][c] = ch[r][c] = v.hi;
+            sl[r][c] = cl[r][c] = v.lo;
+          }
+        __syncthreads();                         // (the staging is free again)
+      }
+    }
+    if (!KS || tid < (BM / RM) * (BM / RM))      // (the threads that hold the sums)
+      dd_tile_epilogue<BM, BM, RM, RM, SPLIT>(p, i0, j0, z, ch, cl, wanted);
+    return;
+  }
+  const int count = mine;
+  for (int w = wave; w < count; w += 4) {
+    const int64_t i = i0 + list[w] % BM, j = j0 + list[w] / BM;
+    ddv acc{0.0, 0.0};
+    auto term = [&](int64_t l, ddv& a, ddv& b) {
+      const int64_t oa = TA ? l + i * p.lda : i + l * p.lda;
+      const int64_t ob = TB ? j + l * p.ldb : l + j * p.ldb;
+      a = ddv{p.a_hi[oa], p.a_lo[oa]};
+      b = ddv{p.b_hi[ob], p.b_lo[ob]};
+    };
+    int64_t l = lane;
+    for (; l + 64 * (U - 1) < p.k; l += 64 * U) {     // U terms' loads at a time
+      ddv a[U], b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) term(l + 64 * u, a[u], b[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc = dd_add(acc, dd_mul(a[u], b[u]));
+    }
+    for (; l < p.k; l += 64) {
+      ddv a, b;
+      term(l, a, b);
+      acc = dd_add(acc, dd_mul(a, b));
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+      acc = dd_add(acc, ddv{__shfl_xor(acc.hi, off), __shfl_xor(acc.lo, off)});
+    if (lane == 0) store_entry(p, i, j, acc);
   }
 }
 
@@ -893,8 +871,7 @@ FailedPlan failed_plan(int tri, int64_t m, int64_t n, int64_t k) {
 template <int BM, int RM, bool XM, bool SPLIT>
 static hipError_t launch_failed_t(const GemmParams& p, bool ta, bool tb, const CrtFailed& failed,
                                   const FailedPlan& plan, uint8_t* whole, hipStream_t st) {
-  const int64_t items = (int64_t)plan.blocks * plan.splits;
-  const int grid = (int)std::min<int64_t>(items, BM == 64 ? 1 << 16 : 1024);
+  const int grid = plan.blocks * plan.splits;
   auto kern = !ta ? (!tb ? dd_gemm_failed<BM, RM, XM, false, false, SPLIT>
                          : dd_gemm_failed<BM, RM, XM, false, true, SPLIT>)
                   : (!tb ? dd_gemm_failed<BM, RM, XM, true, false, SPLIT>
