@@ -87,6 +87,8 @@ struct CrtGuard {
   int32_t* mag;                 // a complex product: planes from `plane` on are four magnitude
                                 // products, stored here as they are [4][np][mp]
   int check;                    // block is there already: skip tiles that failed whole
+  int64_t rows, cols;           // of C: skip tiles all of whose rows or columns are refused
+                                // (0: don't look)
 };
 constexpr double CRT_GUARD_MIN_TERMS = 2.0;   // smallest sum (x / 2^sigma)^2 of a row, or
 constexpr double CRT_GUARD_MIN_SUM = 4.0;     // smallest sum |x| / 2^sigma
@@ -290,6 +292,8 @@ struct CrtLong {
   int rbs, cbs;                 // blocks of 32 rows of X and of 64 of Y
   uint8_t* block;               // the guard's block bytes (cleared here) and their number
   int blocks;
+  const float* ythr;            // Y's thresholds, of yused rows
+  int64_t yused;
 };
 constexpr int CRT_LONG_MAX_BITS = 112;          // widest grid: v_3 fits three bytes
 

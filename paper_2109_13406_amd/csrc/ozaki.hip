@@ -743,6 +743,15 @@ oz_gemm_i8_dma(const int8_t* __restrict__ qa, const int8_t* __restrict__ qb,
       if (__ballot(some) == 0) return;
     }
   }
+  // a guarded product: the thresholds of the tile's rows and columns (four a lane,
+  // looked at when the first steps are on their way)
+  float4 trow{}, tcol{};
+  if constexpr (CRT) {
+    if (guard.rows) {
+      if (lane < WM / 4) trow = *(const float4*)(guard.ta + (int64_t)bi * WM + 4 * lane);
+      if (lane < WN / 4) tcol = *(const float4*)(guard.tb + (int64_t)bj * WN + 4 * lane);
+    }
+  }
   // modular form: group d - 2 of crt_group consecutive residue planes; the
   // workgroup multiplies plane ct0 + g of both operands for each g in turn
   // (one k-sweep each, slice it - 1 of both operands below), storing each
@@ -960,6 +969,30 @@ oz_gemm_i8_dma(const int8_t* __restrict__ qa, const int8_t* __restrict__ qb,
 
 #pragma unroll
   for (int q = 0; q < NS - 1; ++q) issue();
+  if constexpr (CRT) {
+    if (guard.rows) {
+      // No row or no column may take this path (nor have its residues been
+      // written): every entry has failed.
+      auto some = [&](const float4& t, int64_t first, int64_t used, int edge) {
+        const int64_t i = first + 4 * lane;
+        return __ballot(lane < edge / 4 &&
+                        ((t.x == t.x && i < used) || (t.y == t.y && i + 1 < used) ||
+                         (t.z == t.z && i + 2 < used) || (t.w == t.w && i + 3 < used))) != 0;
+      };
+      if (!some(trow, i0, guard.rows, WM) || !some(tcol, j0, guard.cols, WN)) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // (the steps' loads into the LDS: vmcnt(0))
+        if (!guard.mag && guard.plane >= ct0 && guard.plane < ct0 + d - 1) {
+          constexpr int ONES = 0x01010101;
+          for (int e = tid; e < WM * WN / 16; e += 64 * NW)
+            *(v4i*)(guard.entry + (j0 + e / (WM / 16)) * mp + i0 + e % (WM / 16) * 16) =
+                v4i{ONES, ONES, ONES, ONES};
+          for (int e = tid; e < (WM / 64) * (WN / 64); e += 64 * NW)
+            guard.block[((j0 >> 6) + e / (WM / 64)) * guard.ldf + (i0 >> 6) + e % (WM / 64)] = 2;
+        }
+        return;
+      }
+    }
+  }
   if constexpr (!PF) {
     // step s: issued 0 .. s + NS - 2, so step s has landed once the loads of
     // NS - 2 later steps remain; no LDS read is in flight at the barrier (the
@@ -1485,11 +1518,18 @@ oz_crt_residues(CrtOperand opa, CrtOperand opb, int blocks_a, int64_t k, int nch
   }
   int ex = 0;
   if (mx != 0.0) frexp(mx, &ex);
+  float thr = 0.0f;
+  if (GUARD) thr = crt_threshold(mx, sum, mags, ex, coef);
   if (l0 == 0 && (tid & 15) == 0) {
     if (r0 + row < rows) op.exps[r0 + row] = ex;
-    if (GUARD) op.thr[r0 + row] = crt_threshold(mx, sum, mags, ex, coef);
+    if (GUARD) op.thr[r0 + row] = thr;
   }
-  __syncthreads();
+  if constexpr (GUARD) {
+    // (no row of these may take the modular route: nobody reads what they hold)
+    if (!__syncthreads_or(r0 + row < rows && thr == thr)) return;
+  } else {
+    __syncthreads();
+  }
   const int lq = (tid & 15) * 8;
   if (l0 + lq >= ldq) return;
   const int sh = p - ex;
@@ -1673,6 +1713,7 @@ oz_crt_combine(const int8_t* __restrict__ x, int64_t mp, int64_t np, int count, 
       cl[r] = c_lo[i + j * ldc];
     }
   }
+  if (__ballot(mine[0] || mine[1]) == 0) return;
   const v4i wt = *(const v4i*)&cst.w[lane & 31][16 * h];
   v16i sd[4];
 #pragma unroll
@@ -1826,6 +1867,12 @@ oz_crt_long(CrtOperand op, CrtLong q) {
   const int64_t r0 = (int64_t)rb * 32, c0 = (int64_t)cb * 64;
   if (blockIdx.x == 0)
     for (int i = tid; i < q.blocks; i += 64 * (LONG_PRODUCTS + LONG_CONVERT)) q.block[i] = 0;
+  bool taken = false;            // a row (tid < 512), a column that may take this path
+  if (tid >= 512 && tid < 576) {
+    const int64_t y = c0 + tid - 512;
+    const float t = q.ythr[y];
+    taken = y < q.yused && t == t;
+  }
   if (tid < 512) {
     // the rows' exponents and thresholds from their chunks' partial values
     const int row = tid >> 4;
@@ -1844,15 +1891,18 @@ oz_crt_long(CrtOperand op, CrtLong q) {
     }
     int ex = 0;
     if (mx != 0.0) frexp(mx, &ex);
+    const float thr = crt_threshold(mx, sum, mags, ex, q.coef);
+    taken = r0 + row < op.rows && thr == thr;
     if ((tid & 15) == 0) {
       rowexp[row] = ex;
       if (cb == 0 && split == 0) {
         if (r0 + row < op.rows) op.exps[r0 + row] = ex;
-        op.thr[r0 + row] = crt_threshold(mx, sum, mags, ex, q.coef);
+        op.thr[r0 + row] = thr;
       }
     }
   }
-  __syncthreads();
+  // (every entry fails by its threshold: what this block would store is not read)
+  if (!__syncthreads_or(tid < 512 && taken) || !__syncthreads_or(tid >= 512 && taken)) return;
 
   const int s0 = split * q.steps_per;
   const int s1 = min(q.steps, s0 + q.steps_per);
@@ -2076,6 +2126,7 @@ oz_crt_combine_c(const int8_t* __restrict__ x, int64_t mp, int64_t np, int count
     }
     *(uint32_t*)(guard.entry + j * mp + i0) = failed;
     if (failed) guard.block[(j >> 6) * guard.ldf + (i0 >> 6)] = 1;
+    if (failed == 0x01010101u) return;
   }
   double sr[4][L], si[4][L];
 #pragma unroll
@@ -2670,6 +2721,8 @@ static int ozaki_crt_gemm(const mpdd_opts* opts, bool guarded, int tri, bool ta,
   if (guarded) {
     guard = crt_guard_at(take(g_bytes), mp, np, A, B);
     guard.plane = count;
+    guard.rows = m;
+    guard.cols = n;
     if (tri) {                    // op(B)'s columns are op(A)'s rows
       guard.tb = guard.ta;
       guard.bb = guard.ba;
@@ -2817,6 +2870,8 @@ int ozaki_guarded_long_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, d
   crt_set_parts(X, take(px_bytes));
   crt_set_parts(Y, take(py_bytes));
   const CrtGuard guard = crt_guard_at(take(g_bytes), mp, np, A, B);
+  q.ythr = Y.thr;
+  q.yused = Y.rows;
   q.block = guard.block;
   q.blocks = (int)((mp / 64) * (np / 64));
   launch_crt_scale(X, &Y, k, st);
@@ -2912,6 +2967,8 @@ int ozaki_crt_cgemm(const void* opts_v, bool guarded, int opa, int opb, int64_t 
     guard = crt_guard_at(mag + 4 * mp * np, mp, np, A, B);
     guard.mag = mag;
     guard.plane = 3 * count;
+    guard.rows = m;
+    guard.cols = n;
     coef = (float)(1.02 * std::ldexp(1.0, 117 - p));
     A.mag = qa + 3 * sa; A.mag2 = A.mag + 2 * ga;
     B.mag = qb + 3 * sb; B.mag2 = B.mag + 3 * gb;
