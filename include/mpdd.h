@@ -93,7 +93,8 @@ int mpdd_destroy(mpdd_handle h);
  *
  * Without options (here, in mpdd_Rsyrk, mpdd_Cgemm and mpdd_Qgemm, and in the _ex forms
  * with opts NULL) the library chooses the algorithm by estimated time: the
- * plain dd multiply-accumulate (MPDD_PLAIN), or the modular form on the
+ * plain dd multiply-accumulate (MPDD_PLAIN; with the tile and k-split of the handle's
+ * tuning table, if it has them for this size), or the modular form on the
  * matrix cores with its grid widened to 109 bits or more (mpdd_Cgemm: the
  * complex one), behind a guard that bounds every entry's error on the device
  * and leaves the entries whose bound is not within the plain product's to the

@@ -34,14 +34,15 @@ extern "C" {
  * per-group latency (seconds).  Returns 0 or MPDD_ERR_ARG. */
 int mpdd_server_set_fake_rate(mpdd_server s, double dd_flops_per_s, double group_latency_s);
 
-/* The way that a call without options takes, by size alone (not under capture,
- * scratch to be had): 0 the plain kernels, 1 the guarded modular form, 2 its form
- * for one long operand.  op: MPDD_OP_GEMM or MPDD_OP_SYRK, or MPDD_TEST_CGEMM or
+/* The way that a call without options on untransposed operands takes (not under
+ * capture, scratch to be had): 0 the plain kernels, 1 the guarded modular form, 2
+ * its form for one long operand.  h may be NULL: a handle without a tuning table.  op: MPDD_OP_GEMM or MPDD_OP_SYRK, or MPDD_TEST_CGEMM or
  * MPDD_TEST_QGEMM (m, n, k of the product, Rsyrk m = n).  tile, splitk (may be
  * NULL): the plain kernels' tile-table entry and k-split of that size. */
 #define MPDD_TEST_CGEMM 16
 #define MPDD_TEST_QGEMM 17
-int mpdd_test_route(int op, mpdd_int m, mpdd_int n, mpdd_int k, int *tile, int *splitk);
+int mpdd_test_route(mpdd_handle h, int op, mpdd_int m, mpdd_int n, mpdd_int k, int *tile,
+                    int *splitk);
 
 #ifdef __cplusplus
 }

@@ -143,7 +143,7 @@ SIGNATURES = {
     "mpdd_server_poll": (ctypes.c_int, [_P, ctypes.c_uint64, ctypes.POINTER(ctypes.c_int)]),
     "mpdd_server_get_stats": (ctypes.c_int, [_P, ctypes.POINTER(mpdd_server_stats)]),
     "mpdd_server_destroy": (ctypes.c_int, [_P]),
-    "mpdd_test_route": (ctypes.c_int, [ctypes.c_int, _I, _I, _I, ctypes.POINTER(ctypes.c_int),
+    "mpdd_test_route": (ctypes.c_int, [_P, ctypes.c_int, _I, _I, _I, ctypes.POINTER(ctypes.c_int),
                                        ctypes.POINTER(ctypes.c_int)]),
     "mpdd_tile_count": (ctypes.c_int, []),
     "mpdd_tile_info": (ctypes.c_int, [ctypes.c_int] + [ctypes.POINTER(ctypes.c_int)] * 4),
@@ -608,11 +608,11 @@ def mpdd_server_create(h, hbm_budget_bytes, max_inflight, flags=0):
     return s
 
 
-def mpdd_test_route(op, m, n, k):
+def mpdd_test_route(op, m, n, k, h=None):
     """(route, tile, splitk): 0 plain, 1 guarded modular, 2 its long form, of a
     call without options; the tile and k-split of the plain kernels."""
     tile, split = ctypes.c_int(), ctypes.c_int()
-    route = load().mpdd_test_route(op, m, n, k, ctypes.byref(tile), ctypes.byref(split))
+    route = load().mpdd_test_route(h, op, m, n, k, ctypes.byref(tile), ctypes.byref(split))
     return route, tile.value, split.value
 
 

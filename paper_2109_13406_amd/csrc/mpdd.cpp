@@ -334,8 +334,9 @@ int run_plain(mpdd_handle h, const mpdd_opts* o, bool ta, bool tb, int tri, int6
 // uniform data at k = 256; of data spread over 40 binades 0.1 % of the entries
 // fail at k = 512, 3 % at k = 256.
 //
-// Which way: the least of the three estimated times (plain kernels, modular form,
-// its form for one long operand), the modular ones times an allowance for
+// Which way: the least of the three estimated times (plain kernels, with the tile
+// and k-split of the handle's tuning table if it has them for this size; modular
+// form; its form for one long operand), the modular ones times an allowance for
 // the entries that fail in data spread over 40 binades: such data take 2 to 3
 // times the uniform time at k = 256 .. 300 (2000^2 x 300: 670 us against 227, plain
 // 460), 1.9 at 350, 1.5 at 400, 1.15 to 1.3 at 512 and 1.05 at 1024, and must not
@@ -348,10 +349,23 @@ double guard_allowance(int64_t k) {
   return k < 400 ? 1.9 : k < 512 ? 1.4 : k < 1024 ? 1.1 : 1.0;
 }
 
-Route default_route(int tri, int64_t m, int64_t n, int64_t k) {
+// The plain kernels' estimated time on this handle (null: without a table; an
+// entry whose tile has no estimate: the built-in choice's).
+double plain_us(const mpdd_handle_s* h, int tri, bool ta, bool tb, int64_t m, int64_t n,
+                int64_t k) {
+  TuneEntry e;
+  if (h && h->tune.lookup(tri ? 1 : 0, ta, tb, m, n, k, e)) {
+    const double us = estimated_us(e.tile, m, n, k, tri != 0, std::max(1, e.splitk));
+    if (us > 0.0) return us;
+  }
+  return default_plan(m, n, k, tri != 0, 32).us;
+}
+
+Route default_route(const mpdd_handle_s* h, int tri, bool ta, bool tb, int64_t m, int64_t n,
+                    int64_t k) {
   if (k < 350) return Route::plain;
   const double allow = guard_allowance(k);
-  const double plain = default_plan(m, n, k, tri != 0, 32).us;
+  const double plain = plain_us(h, tri, ta, tb, m, n, k);
   const double wide = guarded_us(tri, m, n, k);
   const double lng = tri ? 1e30 : guarded_long_us(m, n, k);
   if (allow * std::min(wide, lng) >= plain) return Route::plain;
@@ -371,10 +385,10 @@ bool qd_guarded_shape(int64_t m, int64_t n, int64_t k) {
 // The guard is the real one with Q over both parts of a row; an entry is taken if
 // both |Ar||Br| + |Ai||Bi| and |Ar||Bi| + |Ai||Br| pass.  1024^3: 345 us, four
 // guarded real products 479, four plain ones 1490.
-bool complex_route(int64_t m, int64_t n, int64_t k) {
+bool complex_route(const mpdd_handle_s* h, bool ta, bool tb, int64_t m, int64_t n, int64_t k) {
   if (k < 350) return false;
   const double allow = guard_allowance(k);
-  const double four = 4.0 * std::min({default_plan(m, n, k, false, 32).us,
+  const double four = 4.0 * std::min({plain_us(h, 0, ta, tb, m, n, k),
                                       allow * guarded_us(0, m, n, k),
                                       allow * guarded_long_us(m, n, k)});
   return allow * guarded_complex_us(m, n, k) < four;
@@ -384,7 +398,8 @@ int run_default(mpdd_handle h, bool ta, bool tb, int tri, int64_t m, int64_t n, 
                 mpdd_dd alpha, const double* Ah, const double* Al, int64_t lda, const double* Bh,
                 const double* Bl, int64_t ldb, mpdd_dd beta, double* Ch, double* Cl, int64_t ldc,
                 hipStream_t st) {
-  const Route route = is_zero(alpha) ? Route::plain : default_route(tri, m, n, k);
+  const Route route = is_zero(alpha) ? Route::plain
+                                      : default_route(h, tri, ta, tb, m, n, k);
   if (route != Route::plain && !ScratchCache::capturing(st)) {
     const int rc =
         route == Route::guarded
@@ -470,14 +485,20 @@ int mpdd_ozaki_split(mpdd_handle h, int algo, const char* trans, mpdd_int rows, 
                            rows_p, (hipStream_t)stream, h->scratch);
 }
 
-int mpdd_test_route(int op, mpdd_int m, mpdd_int n, mpdd_int k, int* tile, int* splitk) {
+int mpdd_test_route(mpdd_handle h, int op, mpdd_int m, mpdd_int n, mpdd_int k, int* tile,
+                    int* splitk) {
   const bool tri = op == MPDD_OP_SYRK;
-  const TilePlan plan = default_plan(m, n, k, tri, 32);
+  TilePlan plan = default_plan(m, n, k, tri, 32);
+  TuneEntry e;
+  if (h && h->tune.lookup(tri ? 1 : 0, false, tri, m, n, k, e)) {
+    plan.tile = e.tile;
+    plan.splitk = e.splitk;
+  }
   if (tile) *tile = plan.tile;
   if (splitk) *splitk = plan.splitk;
-  if (op == MPDD_TEST_CGEMM && complex_route(m, n, k)) return 1;
+  if (op == MPDD_TEST_CGEMM && complex_route(h, false, false, m, n, k)) return 1;
   if (op == MPDD_TEST_QGEMM) return qd_guarded_shape(m, n, k) ? 1 : 0;
-  return (int)default_route(tri, m, n, k);
+  return (int)default_route(h, tri, false, tri, m, n, k);
 }
 
 int mpdd_create(mpdd_handle* h, const char* tuner_cache_path) {
@@ -665,7 +686,7 @@ int mpdd_Cgemm_ex(mpdd_handle h, const mpdd_opts* opts, const char* transa, cons
   const size_t plane = (size_t)m * (size_t)n * sizeof(double);
   const mpdd_dd zero{0.0, 0.0}, one{1.0, 0.0};
   e.ldp = m;
-  const bool guarded = !opts && complex_route(m, n, k) && !ScratchCache::capturing(st);
+  const bool guarded = !opts && complex_route(h, ta, tb, m, n, k) && !ScratchCache::capturing(st);
   if (algo == MPDD_OZAKI_CRT || guarded) {
     // modular form: the complex product from three residue products per
     // modulus, exact in integers, into P; then the same complex epilogue

@@ -103,6 +103,12 @@ double plan_time(const TileTime& t, int64_t m, int64_t n, int64_t k, bool tri, i
 
 }  // namespace
 
+double estimated_us(int tile, int64_t m, int64_t n, int64_t k, bool tri, int splitk) {
+  for (const TileTime& t : kTileTimes)
+    if (t.tile == tile) return plan_time(t, m, n, k, tri, splitk);
+  return 0.0;
+}
+
 int default_split(int64_t tiles, int64_t k, bool tri) {
   const int64_t target = tri ? 2048 : 1024, min_range = tri ? 512 : 256;
   int s = 1;

@@ -45,6 +45,8 @@ struct TilePlan {
 };
 int default_split(int64_t tiles, int64_t k, bool tri);   // k-split of a named tile
 TilePlan default_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split);
+// The estimated time of a tile-table entry with a k-split (0: none for this entry).
+double estimated_us(int tile, int64_t m, int64_t n, int64_t k, bool tri, int splitk);
 // (by the time alone, of the square tiles up to max_edge with splits up to max_split)
 TilePlan timed_plan(int64_t m, int64_t n, int64_t k, bool tri, int max_split, int max_edge = 64);
 int default_tile(int64_t m, int64_t n, int64_t k, bool tri);
