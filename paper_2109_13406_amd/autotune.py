@@ -75,14 +75,31 @@ def tune_shape(h, op, ta, tb, m, n, k, reps=3, splits=(1, 2, 4, 8, 16), verbose=
     return best, results
 
 
-SERVE_TILES = (2, 4)   # tile entries the request server's grouped launches run (unsplit)
+SERVE_TILES = (2, 4, 5)   # tile entries the request server's grouped launches run (unsplit)
+SERVE_EDGES = (32, 64, 16)
 
 
-def serve_best(results):
-    """Fastest unsplit candidate among the tiles the server runs (None if
-    none was timed)."""
+# How much slower alone a tile may be timed and still be taken for its size: a
+# larger one does the same work in less of the chip's time.  (3000 requests of the
+# serving stream: with the fastest tile always, back to back 4.34 dd-TFLOPS; within
+# 15 % 4.5 to 4.6, p50 at 1000/s 0.048 ms both; within 80 % 4.81, p50 0.054 and p99
+# 1.0 instead of 0.82 ms; with 32 x 32 tiles alone 4.7, p50 0.069.)  Requests that leave most of the chip idle take the smaller
+# one: their kernel times differ by more than the timed calls, which wait for the host.
+SERVE_SLACK = 1.15
+
+
+def serve_best(results, m, n):
+    """Unsplit candidate for the server among the tiles it runs (None if none was
+    timed), for an m x n result: of those that alone take at most SERVE_SLACK times
+    the fastest one's time the largest tile, or the smallest if 64 of it (16 x 16)
+    are enough, a quarter of the CUs."""
     cand = [r for r in results if r["splitk"] == 1 and r["tile"] in SERVE_TILES]
-    return min(cand, key=lambda r: r["seconds"]) if cand else None
+    if not cand:
+        return None
+    fastest = min(r["seconds"] for r in cand)
+    idle = -(-m // 16) * -(-n // 16) <= 64
+    return max((r for r in cand if r["seconds"] <= SERVE_SLACK * fastest),
+               key=lambda r: SERVE_EDGES[SERVE_TILES.index(r["tile"])] * (-1 if idle else 1))
 
 
 def tune_ozaki(h, n, kind="i8", slices=(13, 16), reps=2, verbose=True):
@@ -170,7 +187,7 @@ def main():
         best, res = tune_shape(h, op, ta, tb, m, n, k, reps=args.reps)
         print(f"BEST {op} {ta}{tb} {m}x{n}x{k}: tile {best['tile']} split {best['splitk']} "
               f"{best['dd_gflops']:.1f} dd-GFLOPS", flush=True)
-        sb = serve_best(res)
+        sb = serve_best(res, m, n)
         combos = ("NN", "NT", "TN", "TT") if op == "gemm" else ("NT", "TN")
         for tr in combos:
             entries.append(dict(op=op, trans=tr, mb=bucket(m), nb=bucket(n), kb=bucket(k),
