@@ -139,8 +139,9 @@ def bench_plain(h, args, stream):
 
 def bench_sizes(h, args, stream):
     """The other products of the Rgemm size sweep (square NN and TN at
-    1024 .. 4096, the 4096 x 4096 x 256 and 8192 x 64 x 8192 shapes), default
-    tile and k-split choice, padded leading dimensions."""
+    1024 .. 4096, the 4096 x 4096 x 256 and 8192 x 64 x 8192 shapes) by calls
+    without options (the library's choice of algorithm, tile and k-split), padded
+    leading dimensions."""
     import torch
     import workloads as W
     from paper_2109_13406_amd import binding as b
@@ -381,8 +382,9 @@ def verify_served(arena, samples=8, seed=0):
 def bench_syrk(h, args, stream):
     """Rsyrk: the headline shape (U N, n = k = args.n) and every config-2
     variant, uplo U/L x trans N/T x n in {2048, 8192} x k in {512, 8192},
-    with a random dd beta (C read) and the opposite triangle NaN-sentinelled.
-    dd-flops n(n+1)k."""
+    with a random dd beta (C read) and the opposite triangle NaN-sentinelled, by
+    calls without options (the library's choice of algorithm); plain_ms: the
+    headline shape on the plain kernels.  dd-flops n(n+1)k."""
     import torch
     import workloads as W
     from paper_2109_13406_amd import binding as b
@@ -409,11 +411,21 @@ def bench_syrk(h, args, stream):
                 if n == k == args.n and uplo == "U" and trans == "N":
                     out["workload"] = f"Rsyrk U N n={n} k={k} ld={W.ld_padded(n)}"
                     out["ms"], out["dd_gflops"] = rec["ms"], rec["dd_gflops"]
+
+                    def plain_step():
+                        info = b.mpdd_Rsyrk_ex(h, dict(algo=b.MPDD_PLAIN), uplo, trans, n, k,
+                                               case["alpha"], case["A"], case["lda"],
+                                               case["beta"], case["C"], case["ldc"],
+                                               stream=stream)
+                        if info != 0:
+                            raise RuntimeError(f"mpdd_Rsyrk_ex info={info}")
+                    _, per = timed_calls(plain_step, steps, 1, stream)
+                    out["plain_ms"] = round(sum(per) / len(per) * 1e3, 3)
                 log(f"rsyrk {rec}")
                 del case
                 torch.cuda.empty_cache()
-    out["split_i8"] = bench_syrk_split(h, args, stream, out.get("ms"), "i8")
-    out["split_crt"] = bench_syrk_split(h, args, stream, out.get("ms"), "crt")
+    out["split_i8"] = bench_syrk_split(h, args, stream, out.get("plain_ms"), "i8")
+    out["split_crt"] = bench_syrk_split(h, args, stream, out.get("plain_ms"), "crt")
     return out
 
 
@@ -471,9 +483,10 @@ def bench_syrk_split(h, args, stream, plain_ms, kind):
 
 
 def bench_cgemm(h, args, stream):
-    """Complex dd Cgemm NN at n/2: four-product (default) and three-product
-    plain forms, the four products in the INT8 split form, and the complex
-    modular form (three residue products per modulus).  Complex flops: 8 mnk (LAWN 41: 6 real multiplies + 2 adds per
+    """Complex dd Cgemm NN at n/2: four-product and three-product plain forms,
+    the four products in the INT8 split form, the complex modular form (three
+    residue products per modulus), and the call without options (the library's
+    choice).  Complex flops: 8 mnk (LAWN 41: 6 real multiplies + 2 adds per
     complex multiply-add), for both forms."""
     import torch
     import workloads as W
@@ -483,7 +496,8 @@ def bench_cgemm(h, args, stream):
     torch.cuda.synchronize()
     out = {"workload": f"Cgemm NN m=n=k={n} ld={W.ld_padded(n)} (four real dd planes each)"}
     C0 = tuple(x.clone() for x in case["C"])
-    for form, opts in (("4m", None), ("3m", dict(algo=b.MPDD_COMPLEX_3M)),
+    for form, opts in (("default", None), ("4m", dict(algo=b.MPDD_PLAIN)),
+                       ("3m", dict(algo=b.MPDD_COMPLEX_3M)),
                        ("split_i8", dict(algo=b.MPDD_OZAKI_I8, nslices=12)),
                        ("split_crt", dict(algo=b.MPDD_OZAKI_CRT, nslices=CRT_MODULI))):
         # one call from the saved C, checked against the CPU oracle on 32 x 32
@@ -772,7 +786,8 @@ def bench_ozaki(h, args, stream, t_plain_main):
             args_ = ("N", "N", n, n, n, case["alpha"], case["A"], case["lda"], case["B"],
                      case["ldb"], case["beta"])
             P = tuple(x.clone() for x in C0)
-            plain = lambda: b.mpdd_Rgemm(h, *args_, P, case["ldc"], stream=stream)
+            on_plain = dict(algo=b.MPDD_PLAIN)
+            plain = lambda: b.mpdd_Rgemm_ex(h, on_plain, *args_, P, case["ldc"], stream=stream)
             assert plain() == 0
             plain_vs_oracle = oracle_compare(smp, P)
             if n == args.n:
@@ -781,7 +796,8 @@ def bench_ozaki(h, args, stream, t_plain_main):
                 # timed on a copy: each timed call updates its C again, and P
                 # must stay the result of one call
                 Pt = tuple(x.clone() for x in C0)
-                plain_t = lambda: b.mpdd_Rgemm(h, *args_, Pt, case["ldc"], stream=stream)
+                plain_t = lambda: b.mpdd_Rgemm_ex(h, on_plain, *args_, Pt, case["ldc"],
+                                                  stream=stream)
                 _, per = timed_calls(plain_t, 3, 1, stream)
                 t_plain = sum(per) / len(per)
                 del Pt
