@@ -150,8 +150,12 @@ __device__ __forceinline__ void qd_add(qacc& c, const qacc& o) {
   qd_renorm(c);
 }
 
-// Failed entries of a tile above which it is computed whole.
-constexpr int QD_FAILED_ENTRIES = 256;
+// Failed entries of a tile above which it is computed whole (a tile takes its
+// workgroup 1.05 us a term, an entry its wave 3.5 us at k = 96 and 4.7 at 200; at
+// least a row and a column of the tile).  With 256, all of 200^3 failed took 300 us on
+// top of the modular product's 71: 256 single entries in each tile of the last 8
+// columns.  With 96: 200 us.
+constexpr int QD_FAILED_ENTRIES = 96;
 
 // The entries of C that a guarded modular product left to the plain one, as
 // dd_gemm_failed, in units of one 32 x 32 tile.

@@ -203,3 +203,36 @@ def test_refused_entries_round_no_more_than_the_plain_product(h, m, n, k):
         C = [W.view(x, m, n, case["ldc"]) for x in C]
         rms.append(np.sqrt(np.mean(_exact_errors(A, B, C, rows, cols) ** 2)))
     assert rms[1] <= 1.15 * rms[0], rms
+
+
+@pytest.mark.parametrize("m,n,k", [(200, 200, 200), (200, 96, 130), (72, 131, 300)])
+def test_failed_entries_qgemm(h, m, n, k):
+    """All entries failed (spread operands): tiles with more than 96 of them, the
+    narrow ones at the edges included, are the plain kernel's bit for bit."""
+    import torch
+    from paper_2109_13406_amd import binding as b
+    assert b.mpdd_test_route(b.MPDD_TEST_QGEMM, m, n, k)[0] == 1
+    c = W.qgemm_case(7995, "N", "N", m, n, k)
+    s = 2.0 ** np.round(np.linspace(0, -100, k))
+    for x in c["A"]:
+        W.view(x, m, k, c["lda"])[:] *= s
+    for x in c["B"]:
+        W.view(x, k, n, c["ldb"])[:] /= s[:, None]
+    dA, dB, dC = ([torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in c[y]] for y in "ABC")
+    out = []
+    for opts in (dict(algo=b.MPDD_PLAIN), None):
+        C = [x.clone() for x in dC]
+        assert b.mpdd_Qgemm(h, "N", "N", m, n, k, c["alpha"], dA, c["lda"], dB, c["ldb"],
+                            c["beta"], C, c["ldc"], opts=opts) == 0
+        torch.cuda.synchronize()
+        out.append([W.view(x.cpu().numpy(), m, n, c["ldc"]) for x in C])
+    tile = lambda size: np.minimum(32, size - np.arange(size) // 32 * 32)
+    whole = tile(m)[:, None] * tile(n)[None, :] > 96
+    for p, g in zip(*out):
+        assert np.array_equal(bits(p[whole]), bits(g[whole]))
+    d = sum(g - p for p, g in zip(*out))
+    unit = 2.0 ** -209 * (abs(c["alpha"][0]) *
+                          (np.abs(W.view(c["A"][0], m, k, c["lda"])) @
+                           np.abs(W.view(c["B"][0], k, n, c["ldb"]))) +
+                          abs(c["beta"][0]) * np.abs(W.view(c["C"][0], m, n, c["ldc"])))
+    assert np.max(np.abs(d) / unit) <= 2 * (k + 8)
