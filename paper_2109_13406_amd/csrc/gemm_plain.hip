@@ -18,8 +18,8 @@
 //
 // With a k-split (skinny products with too few C tiles to fill 256 CUs),
 // blockIdx.z selects a k-range; each slice writes its dd partial sums to a
-// scratch buffer and dd_splitk_reduce adds them in a fixed order with
-// cross-lane shuffles, then applies alpha / beta.
+// scratch buffer and dd_splitk_reduce, a thread an entry, adds them in a fixed
+// order, then applies alpha / beta.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -634,8 +634,7 @@ dd_gemm_kernel(GemmParams p) {
 // of (request, tile) work items (sorted longest first), workgroup g taking
 // items g, g + G, g + 2G, ...  Each item runs exactly the steps of
 // dd_gemm_kernel for that request's flags, so a request's result is bit-
-// identical to a standalone call with the same tile.  The item count is read
-// from the device header, so one captured launch serves every group.
+// identical to a standalone call with the same tile.
 template <int BM, int BN, int BK, int RM, int RN, bool XM>
 __global__ void __launch_bounds__((BM / RM) * (BN / RN))
 dd_grouped_kernel(const char* __restrict__ base, const ServeReq* __restrict__ reqs,

@@ -55,8 +55,9 @@ hipError_t launch_gemm(int tile, const GemmParams& p, bool ta, bool tb, bool acc
                        int splitk, hipStream_t st);
 // Entries of C that a guarded modular product left to the plain one:
 // entry[j*lde + i] = 1 (else 0; stored for the whole tiles of the product),
-// block[bj*ldf + bi] = 0 / 1 / 2 where no, some or all entries of the 64 x 64
-// block (bi, bj) are.
+// block[bj*ldf + bi] = 0 where no entry of the 64 x 64 block (bi, bj) is, else 1,
+// or 2 (the real dd and the qd form, not the long and the complex one) where all
+// are, those past C's edges included.
 struct CrtFailed {
   const uint8_t *block, *entry;
   int64_t ldf, lde;
@@ -78,8 +79,7 @@ hipError_t launch_gemm_failed(const GemmParams& p, bool ta, bool tb, const CrtFa
 hipError_t launch_splitk_reduce(const GemmParams& p, int splitk, hipStream_t st);
 // Persistent grouped kernel over the `which`-th item list: counts[c] items per
 // tile shape, lists stored back to back starting at base + *items_offset
-// (counts and offset are read on the device, so a captured launch serves
-// every group).
+// (read on the device).
 hipError_t launch_grouped_list(int tile, const char* base, const ServeReq* reqs,
                                const int* counts, const int* items_offset, int which, int grid,
                                hipStream_t st);
@@ -164,9 +164,12 @@ int ozaki_guarded_gemm(int tri, bool ta, bool tb, int64_t m, int64_t n, int64_t 
                        double beta_hi, double beta_lo, double* c_hi, double* c_lo, int64_t ldc,
                        hipStream_t st, ScratchCache& pool);
 // Estimated time (us) of the guarded modular product: of all launches by the
-// entries read (residues) and written, and the products' rounds; within 20 % of
-// measured from 400^3 to 8192^3.  And of the complex product and of
-// the form for a long and a short operand (1e30: not applicable).
+// entries read (residues) and written, and the products' rounds.  The kernels have
+// become faster since it was fitted: estimated and measured 74 and 60 at 600^3, 140
+// and 105 at 1024^3, 596 and 461 at 2048^3, 3585 and 2632 at 4096^3, so that near the
+// line the plain kernels are taken.  And of the complex product (126 and 136 at
+// 512^3, 399 and 318 at 1024^3) and of the form for a long and a short operand (123 and
+// 99 at 1031 x 64 x 4001, 704 and 706 at 8192 x 64 x 8192; 1e30: not applicable).
 double guarded_us(int tri, int64_t m, int64_t n, int64_t k);
 double guarded_complex_us(int64_t m, int64_t n, int64_t k);
 double guarded_long_us(int64_t m, int64_t n, int64_t k);

@@ -329,18 +329,24 @@ int run_plain(mpdd_handle h, const mpdd_opts* o, bool ta, bool tb, int tri, int6
 // floor(|x| 2^(7 - sigma)) of both operands make one more INT8 product G, with
 // (|A||B|)_ij >= G_ij 2^(sigma_i + tau_j - 14).  Entries that fail, and rows or
 // columns that are not finite, near the ends of the exponent range, not
-// normalised, or of few terms (Q^2 < 2: identities, permutations, whose plain
-// products are exact) are computed plainly.  P >= 109 leaves a factor of 50 for
-// uniform data at k = 256; of data spread over 40 binades 0.1 % of the entries
-// fail at k = 512, 3 % at k = 256.
+// normalised, or of few terms (identities, permutations, whose plain products are
+// exact: crt_threshold in ozaki.hip) are computed plainly.  P >= 109 leaves a factor
+// of 50 for uniform data at k = 256; of data spread over 40 binades 0.1 % of the
+// entries fail at k = 512, 3 % at k = 256.
+//
+// What it costs where it refuses (us; default, plain).  Every row refused, identity:
+// 600^3 143, 93; 1024^3 410, 358; 4096^3 20300, 20000.  Every entry refused by its own
+// bound, scalings of A and B that cancel, where all of the modular product is done
+// first: 600^3 166, 103; 1024^3 511, 366; 4096^3 23900, 21200; 1031 x 64 x 4001 225, 114;
+// 8192 x 64 x 8192 2400, 1420.  A Cholesky factor times a full matrix 307 to 371, 360
+// at 1024^3, times another one 470.
 //
 // Which way: the least of the three estimated times (plain kernels, with the tile
 // and k-split of the handle's tuning table if it has them for this size; modular
 // form; its form for one long operand), the modular ones times an allowance for
-// the entries that fail in data spread over 40 binades: such data take 2 to 3
-// times the uniform time at k = 256 .. 300 (2000^2 x 300: 670 us against 227, plain
-// 460), 1.9 at 350, 1.5 at 400, 1.15 to 1.3 at 512 and 1.05 at 1024, and must not
-// lose by the route.  Examples (plain, modular, long form, us): 512^3 63, 57, 96;
+// the entries that fail in data spread over 40 binades, which must not lose by the
+// route: such data take 1.7 times the uniform time at k = 350 (2048^2: 296 us against
+// 174, plain 482), 1.3 to 1.5 at 400, 1.2 at 512 and 1.07 at 1024.  Examples (plain, modular, long form, us): 512^3 63, 57, 96;
 // 700 x 200 x 2000 137, 92, 122; 405 x 1167 x 832 176, 94, -; 8192 x 64 x 8192 1430,
 // 1400, 700; 400^3 43, 57, 108.
 enum class Route { plain, guarded, guarded_long };
@@ -383,7 +389,7 @@ bool qd_guarded_shape(int64_t m, int64_t n, int64_t k) {
 // Whether a complex product takes the guarded complex form (one conversion of
 // each part, three products a modulus) or four real products by default_route.
 // The guard is the real one with Q over both parts of a row; an entry is taken if
-// both |Ar||Br| + |Ai||Bi| and |Ar||Bi| + |Ai||Br| pass.  1024^3: 345 us, four
+// both |Ar||Br| + |Ai||Bi| and |Ar||Bi| + |Ai||Br| pass.  1024^3: 318 us, four
 // guarded real products 479, four plain ones 1490.
 bool complex_route(const mpdd_handle_s* h, bool ta, bool tb, int64_t m, int64_t n, int64_t k) {
   if (k < 350) return false;
@@ -631,9 +637,10 @@ int mpdd_Rsyrk_ex(mpdd_handle h, const mpdd_opts* opts, const char* uplo, const 
                    C_hi, C_lo, ldc, (hipStream_t)stream);
 }
 
-// Cgemm.  With sA = -1 when op(A) conjugates (transa 'C'), else +1, and
+// Cgemm.  Without options by complex_route (above): the guarded complex modular form,
+// or 4M with real products by default_route.  With sA = -1 when op(A) conjugates (transa 'C'), else +1, and
 // op_r(A), op_i(A) the real transposition of the real and imaginary planes:
-//  4M (default):
+//  4M (MPDD_PLAIN):
 //   Re P = op_r(Ar) op_r(Br) - sA sB op_r(Ai) op_r(Bi)
 //   Im P = sB op_r(Ar) op_r(Bi) + sA op_r(Ai) op_r(Br),
 //   four plain dd products (the second of each pair accumulates onto the first
@@ -1073,8 +1080,9 @@ int mpdd_Rpotrf(mpdd_handle h, const char* uplo, mpdd_int n, double* A_hi, doubl
   return mpdd_Rpotrf_nb(h, uplo, n, A_hi, A_lo, lda, 0, info, stream);
 }
 
-// Quad-double Rgemm: one launch of the qd tile kernel (or the scale kernel
-// when alpha = 0 or k = 0).
+// Quad-double Rgemm: without options the guarded qd modular form where
+// qd_guarded_shape, else one launch of the qd tile kernel (or the scale kernel when
+// alpha = 0 or k = 0).
 int mpdd_Qgemm(mpdd_handle h, const char* transa, const char* transb, mpdd_int m, mpdd_int n,
                mpdd_int k, mpdd_qd alpha, const double* A0, const double* A1, const double* A2,
                const double* A3, mpdd_int lda, const double* B0, const double* B1,

@@ -1835,8 +1835,8 @@ oz_crt_combine(const int8_t* __restrict__ x, int64_t mp, int64_t np, int count, 
 //
 // Bound: the converting waves' vector instructions, one wave a SIMD, 6 clocks each
 // (~1300 a step), 4.5 us a step; the memory time of X is 1.9 us of it.  8192 x 64 x
-// 8192: 580 us, with scale, Y's residues and reconstruction 700 to 760 (plain kernel
-// 1430, pipeline 1390).
+// 8192: 613 us in a trace, with scale, Y's residues and reconstruction 670 to 706
+// (plain kernel 1400, pipeline 1390).
 constexpr int LONG_PRODUCTS = 8, LONG_CONVERT = 4;   // waves of each kind
 
 template <bool SWAP>

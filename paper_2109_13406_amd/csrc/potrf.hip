@@ -35,7 +35,8 @@
 //
 // Bound: the chain of the diagonal block (64 dependent columns of a reciprocal,
 // a multiply, a dd multiply-subtract and a barrier, about 0.8 us each), hidden
-// by nothing: 66 us a block column of 64 at n = 2048, of which 15 are the rows.
+// by nothing: 73 us a block column of 64 at n = 2048 (60 for the last ones), of which
+// 15 are the rows.
 // Before (the elimination of [S | I] in LDS by one workgroup, then a product by
 // the inverse): 76 + 19 us.  With the single-rounding-error "lean" multiply-add
 // the factor's error tripled and the time did not fall, so the accurate
