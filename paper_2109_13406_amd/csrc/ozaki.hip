@@ -2690,11 +2690,8 @@ static int ozaki_crt_gemm(const mpdd_opts* opts, bool guarded, int tri, bool ta,
                        plan.bytes;
   if (guarded && total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
-  if (pool.get(&ws, total, st) != hipSuccess) {
-    if (!guarded) return MPDD_ERR_ALLOC;
-    (void)hipGetLastError();                  // the plain product needs no scratch
-    return MPDD_ERR_SCRATCH;
-  }
+  if (pool.get(&ws, total, st, guarded) != hipSuccess)
+    return guarded ? MPDD_ERR_SCRATCH : MPDD_ERR_ALLOC;    // (the plain product needs none)
   char* at = (char*)ws;
   auto take = [&](size_t bytes) {
     char* q = at;
@@ -2841,10 +2838,7 @@ int ozaki_guarded_long_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, d
                        plan.bytes;
   if (total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
-  if (pool.get(&ws, total, st) != hipSuccess) {
-    (void)hipGetLastError();
-    return MPDD_ERR_SCRATCH;
-  }
+  if (pool.get(&ws, total, st, true) != hipSuccess) return MPDD_ERR_SCRATCH;
   char* at = (char*)ws;
   auto take = [&](size_t bytes) {
     char* r = at;
@@ -2933,11 +2927,8 @@ int ozaki_crt_cgemm(const void* opts_v, bool guarded, int opa, int opb, int64_t 
                        e_bytes + crt_part_bytes(m) + crt_part_bytes(n) + g_bytes + plan.bytes;
   if (guarded && total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
-  if (pool.get(&ws, total, st) != hipSuccess) {
-    if (!guarded) return MPDD_ERR_ALLOC;
-    (void)hipGetLastError();
-    return MPDD_ERR_SCRATCH;
-  }
+  if (pool.get(&ws, total, st, guarded) != hipSuccess)
+    return guarded ? MPDD_ERR_SCRATCH : MPDD_ERR_ALLOC;
   int8_t* qa = (int8_t*)ws;
   int8_t* qb = qa + round_up(qa_bytes, 256);
   int8_t* x = qb + round_up(qb_bytes, 256);
@@ -3044,11 +3035,8 @@ int ozaki_crt_qgemm(const void* opts_v, bool guarded, bool ta, bool tb, int64_t 
                        crt_part_bytes(m) + crt_part_bytes(n) + g_bytes;
   if (guarded && total > CRT_GUARD_SCRATCH) return MPDD_ERR_SCRATCH;
   void* ws = nullptr;
-  if (pool.get(&ws, total, st) != hipSuccess) {
-    if (!guarded) return MPDD_ERR_ALLOC;
-    (void)hipGetLastError();
-    return MPDD_ERR_SCRATCH;
-  }
+  if (pool.get(&ws, total, st, guarded) != hipSuccess)
+    return guarded ? MPDD_ERR_SCRATCH : MPDD_ERR_ALLOC;
   int8_t* qa = (int8_t*)ws;
   int8_t* qb = qa + round_up(qa_bytes, 256);
   int8_t* x = qb + round_up(qb_bytes, 256);

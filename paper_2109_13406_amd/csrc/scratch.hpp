@@ -13,8 +13,8 @@
 // those unused for longest first, when there are more than KEEP of them or they
 // hold more than KEEP_BYTES (one block may hold more by itself: a call that
 // needs it would need it again); when one of the caller's stream is too small;
-// when an allocation fails; and with the handle.  A stream under capture uses
-// the pool itself (its allocations become graph nodes).
+// when an allocation that a call cannot do without fails; and with the handle.  A
+// stream under capture uses the pool itself (its allocations become graph nodes).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -32,8 +32,11 @@ class ScratchCache {
   void open(hipMemPool_t pool) { pool_ = pool; }
 
   // `bytes` bytes for work enqueued on st until put(): *p, or an error with no
-  // error left pending.
-  hipError_t get(void** p, size_t bytes, hipStream_t st) {
+  // error left pending.  `optional`: the caller can do without, so that where there
+  // is no memory nothing is given up or waited for; and after a failed allocation
+  // the next RETRY requests that would make one as large fail at once (a failed
+  // one takes the driver as long as a call).
+  hipError_t get(void** p, size_t bytes, hipStream_t st, bool optional = false) {
     if (capturing(st)) return pool_alloc(p, bytes, st);
     std::lock_guard<std::mutex> lk(mu_);
     Block* own = nullptr;             // the best fit among st's, else its largest
@@ -56,10 +59,21 @@ class ScratchCache {
       return take(*own, p, st);
     }
     if (other) return take(*other, p, st);
-    if (own) drop((size_t)(own - blocks_.data()), st);
+    if (optional && bytes >= refused_ && wait_ > 0) {
+      --wait_;
+      return hipErrorOutOfMemory;
+    }
+    const size_t too_small = own ? (size_t)(own - blocks_.data()) : blocks_.size();
+    if (own && !optional) drop(too_small, st);
     Block b;
     b.bytes = round_size(bytes);
     hipError_t e = pool_alloc(&b.ptr, b.bytes, st);
+    if (optional && e != hipSuccess) {
+      refused_ = bytes;
+      wait_ = RETRY;
+      return e;
+    }
+    if (own && optional) drop(too_small, st);
     if (e != hipSuccess) {
       // hand every free block back and try once more, for the bare size
       for (size_t i = blocks_.size(); i-- > 0;)
@@ -136,6 +150,7 @@ class ScratchCache {
 
  private:
   static constexpr size_t KEEP = 8;
+  static constexpr int RETRY = 64;
   struct Block {
     void* ptr = nullptr;
     size_t bytes = 0;
@@ -204,6 +219,8 @@ class ScratchCache {
   std::mutex mu_;
   hipMemPool_t pool_ = nullptr;
   std::vector<Block> blocks_;
+  size_t refused_ = 0;                // bytes of the last optional allocation that failed
+  int wait_ = 0;                      // requests of that size left to fail at once
 };
 
 }  // namespace mpdd

@@ -118,10 +118,51 @@ static int bounds() {
   return 0;
 }
 
+// Scratch that the caller can do without: where there is no memory nothing that is
+// kept is given up, nothing is waited for, and the driver is not asked every time.
+static int optional() {
+  const size_t MB = (size_t)1 << 20;
+  ScratchCache c;
+  StubStream s;
+  void *p = nullptr, *q = nullptr;
+  CHECK(c.get(&p, 4 * MB, &s) == hipSuccess);
+  CHECK(c.put(p, &s) == hipSuccess);
+  stub::limit = 64 * MB;
+  auto asked = [] { return stub::calls["malloc"]; };
+  auto waits = [] {
+    return stub::calls["wait"] + stub::calls["sync"] + stub::calls["event_sync"] +
+           stub::calls["free"];
+  };
+  int m = asked();
+  const int w = waits();
+  CHECK(c.get(&q, 100 * MB, &s, true) != hipSuccess);
+  CHECK(hipGetLastError() == hipSuccess);
+  CHECK(asked() == m + 1 && waits() == w && stub::live.size() == 1);
+  for (int i = 0; i < 64; ++i) CHECK(c.get(&q, 100 * MB, &s, true) != hipSuccess);
+  CHECK(asked() == m + 1 && waits() == w);
+  CHECK(c.get(&q, 100 * MB, &s, true) != hipSuccess);      // asked again
+  CHECK(asked() == m + 2 && waits() == w && stub::live.size() == 1);
+  // smaller ones and required ones are not held up, and the kept block serves
+  CHECK(c.get(&q, 2 * MB, &s, true) == hipSuccess && q == p);
+  CHECK(c.put(q, &s) == hipSuccess);
+  CHECK(c.get(&q, 32 * MB, &s, true) == hipSuccess);       // (in place of the small one)
+  CHECK(stub::live.size() == 1);
+  CHECK(c.put(q, &s) == hipSuccess);
+  stub::limit = SIZE_MAX;
+  CHECK(c.get(&q, 100 * MB, &s) == hipSuccess);
+  CHECK(c.put(q, &s) == hipSuccess);
+  CHECK(c.get(&q, 100 * MB, &s, true) == hipSuccess);      // its block is kept now
+  CHECK(c.put(q, &s) == hipSuccess);
+  c.close();
+  CHECK(stub::live.empty());
+  return 0;
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!std::strcmp(argv[i], "errors") && errors()) return 1;
     if (!std::strcmp(argv[i], "bounds") && bounds()) return 1;
+    if (!std::strcmp(argv[i], "optional") && optional()) return 1;
   }
   std::printf("ok\n");
   return 0;
