@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <cstddef>
 #include <mutex>
+#include <new>
 #include <vector>
 
 namespace mpdd {
@@ -87,11 +88,18 @@ class ScratchCache {
       Relaxed relaxed;
       e = hipEventCreateWithFlags(&b.done, hipEventDisableTiming);
     }
+    if (e == hipSuccess) {
+      try {
+        blocks_.push_back(b);
+      } catch (const std::bad_alloc&) {        // (none may leave a C entry point)
+        (void)hipEventDestroy(b.done);
+        e = hipErrorOutOfMemory;
+      }
+    }
     if (e != hipSuccess) {
       (void)hipFreeAsync(b.ptr, st);
       return cleared(e);
     }
-    blocks_.push_back(b);
     return take(blocks_.back(), p, st);
   }
 

@@ -1,7 +1,9 @@
 // Bookkeeping of the handle's scratch blocks (scratch.hpp) on the stand-in
 // runtime.  Each argument names a test; the first failing check is printed.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "../../paper_2109_13406_amd/csrc/scratch.hpp"
@@ -15,6 +17,14 @@
   } while (0)
 
 using mpdd::ScratchCache;
+
+static bool no_memory = false;
+void* operator new(size_t n) {
+  if (no_memory && n >= 320) throw std::bad_alloc();   // (a list of eight blocks or more)
+  return std::malloc(n);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 // A failing get or put leaves no error pending and loses no block.
 static int errors() {
@@ -158,11 +168,36 @@ static int optional() {
   return 0;
 }
 
+// No host memory for the list of blocks: an error, not an exception.
+static int host_memory() {
+  StubStream s;
+  ScratchCache c;
+  std::vector<void*> p(40, nullptr);
+  int failed = 0;
+  for (auto& x : p) {
+    no_memory = true;
+    const hipError_t e = c.get(&x, 1 << 20, &s);
+    no_memory = false;
+    if (e != hipSuccess) {
+      x = nullptr;
+      ++failed;
+      CHECK(hipGetLastError() == hipSuccess);
+      CHECK(c.get(&x, 1 << 20, &s) == hipSuccess);
+    }
+  }
+  CHECK(failed > 0 && stub::live.size() == 40);
+  for (auto x : p) CHECK(c.put(x, &s) == hipSuccess);
+  c.close();
+  CHECK(stub::live.empty());
+  return 0;
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!std::strcmp(argv[i], "errors") && errors()) return 1;
     if (!std::strcmp(argv[i], "bounds") && bounds()) return 1;
     if (!std::strcmp(argv[i], "optional") && optional()) return 1;
+    if (!std::strcmp(argv[i], "host_memory") && host_memory()) return 1;
   }
   std::printf("ok\n");
   return 0;

@@ -22,7 +22,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("what", ["errors", "bounds", "optional"])
+@pytest.mark.parametrize("what", ["errors", "bounds", "optional", "host_memory"])
 def test_scratch(exe, what):
     r = subprocess.run([exe, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr[-2000:]
