@@ -646,7 +646,8 @@ def bench_potrf(h, args, stream):
 
 def bench_qd(h, args, stream):
     """Quad-double Rgemm NN at n/4 (four planes per matrix; ~10x the binary64
-    work of a dd multiply-add).  qd-flops 2mnk."""
+    work of a dd multiply-add): the call without options (the library's choice),
+    the plain qd kernel and the split forms.  qd-flops 2mnk."""
     import torch
     import workloads as W
     from paper_2109_13406_amd import binding as b
@@ -692,6 +693,11 @@ def bench_qd(h, args, stream):
            "ms": round(t * 1e3, 3), "qd_gflops": round(2.0 * n ** 3 / t / 1e9, 1),
            "ratio_vs_oracle": round(r, 5),
            "oracle_sample": "24 x 24 entries; normwise, units of k 2^-209"}
+    on_plain = dict(algo=b.MPDD_PLAIN)
+    r = checked(on_plain)
+    t = timed(on_plain)
+    out["plain"] = {"ms": round(t * 1e3, 3), "qd_gflops": round(2.0 * n ** 3 / t / 1e9, 1),
+                    "ratio_vs_oracle": round(r, 5)}
     # split form: slice count searched upward until the sampled entries are
     # within 8 k 2^-209 of the oracle, then timed
     found = None

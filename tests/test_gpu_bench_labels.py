@@ -50,6 +50,19 @@ def test_complex_section_names_its_forms(run):
     assert out["ratio_vs_oracle_4m"] != out["ratio_vs_oracle_default"]
 
 
+def test_qd_section_compares_with_the_plain_kernel(run, monkeypatch):
+    bench, b, h, args, stream, calls = run
+    seen = []
+    real = b.mpdd_Qgemm
+    monkeypatch.setattr(b, "mpdd_Qgemm",
+                        lambda *a, opts=None, **kw: (seen.append(opts), real(*a, opts=opts, **kw))[1])
+    out = bench.bench_qd(h, args, stream)
+    assert None in seen and dict(algo=b.MPDD_PLAIN) in seen
+    for form in ("split_i8", "split_crt"):
+        rec = out[form]
+        assert abs(rec["speedup_vs_plain"] - out["plain"]["ms"] / rec["ms"]) < 0.05
+
+
 def test_syrk_section_gives_the_split_forms_a_plain_time(run, monkeypatch):
     bench, b, h, args, stream, calls = run
     given = []
